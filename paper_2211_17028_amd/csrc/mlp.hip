@@ -12,10 +12,12 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <random>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "tn_internal.h"
@@ -66,11 +68,41 @@ static MlpLayout layout_of(const tn_mlp_shape* s) {
     return L;
 }
 
-// workspace floats for a batch of n: normalized input, activations per hidden
-// layer, output, two gradient buffers, loss partials
-static int64_t ws_floats(const MlpLayout& L, int64_t n) {
-    return n * L.n_in + (int64_t)L.depth * n * L.width + n + 2 * n * std::max(L.width, L.n_in) + 64 +
-           std::max<int64_t>(4096, n / 64 + 64);
+// Output tiles of the weight-gradient launch (64 x 64 weights each) and the
+// number of row ranges a batch of n is split over: enough blocks for two per
+// CU, at least 64 rows each.  One range writes the gradients directly, more
+// write FP64 partials that the reduction adds in range order.
+constexpr int kGradTile = 64;
+static int64_t grad_tiles(const MlpLayout& L) {
+    int64_t t = 0;
+    for (int l = 0; l < L.n_layers; ++l)
+        t += (int64_t)((L.dout[l] + kGradTile - 1) / kGradTile) * ((L.din[l] + kGradTile - 1) / kGradTile);
+    return t;
+}
+static int64_t grad_splits(const MlpLayout& L, int64_t n) {
+    return std::max<int64_t>(1, std::min<int64_t>(512 / grad_tiles(L), n / 64));
+}
+
+// Workspace of a batch of n (float offsets): normalized input, activations of
+// the hidden layers, output, its gradient, gradients of the hidden layers'
+// pre-activations, FP64 loss partials (a block's rows each) and FP64 gradient
+// partials.
+struct MlpWs {
+    int64_t xn, acts, y, dy, dz, part, grad, total;
+};
+static MlpWs ws_layout(const MlpLayout& L, int64_t n) {
+    MlpWs w;
+    auto up = [](int64_t v) { return (v + 63) / 64 * 64; };
+    w.xn = 0;
+    w.acts = up(n * L.n_in);
+    w.y = up(w.acts + (int64_t)L.depth * n * L.width);
+    w.dy = up(w.y + n);
+    w.dz = up(w.dy + n);
+    w.part = up(w.dz + (int64_t)L.depth * n * L.width);
+    w.grad = up(w.part + 2 * ((n + 15) / 16));
+    const int64_t S = grad_splits(L, n);
+    w.total = up(w.grad + (S > 1 ? 2 * S * L.P : 0));
+    return w;
 }
 
 // ---------------------------------------------------------------------------
@@ -178,19 +210,6 @@ __global__ __launch_bounds__(256) void k_loss_grad(const float* y, const float* 
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__global__ __launch_bounds__(256) void k_loss_reduce(const double* part, int nb, int64_t n, float* loss) {
-    __shared__ double red[256];
-    double s = 0;
-    for (int i = threadIdx.x; i < nb; i += 256) s += part[i];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *loss = (float)(red[0] / (double)n);
-}
-
 // dX[n x din] = (dZ[n x dout] W) * (A_prev > 0): gradient through a layer and
 // the previous layer's ReLU (A_prev is that layer's output)
 __global__ __launch_bounds__(256) void k_linear_bwd_data(const float* __restrict__ dZ, const float* __restrict__ W,
@@ -205,35 +224,21 @@ __global__ __launch_bounds__(256) void k_linear_bwd_data(const float* __restrict
     dX[idx] = Aprev[idx] > 0.0f ? s : 0.0f;
 }
 
-// dW[o][i] = sum_r dZ[r][o] A[r][i], db[o] = sum_r dZ[r][o]; one thread per
-// weight (bias when i == din), rows summed in order
-__global__ __launch_bounds__(256) void k_linear_bwd_weight(const float* __restrict__ dZ, const float* __restrict__ A,
-                                                           float* __restrict__ dW, float* __restrict__ db, int64_t n,
-                                                           int din, int dout) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)dout * (din + 1)) return;
-    const int o = (int)(idx / (din + 1));
-    const int i = (int)(idx - (int64_t)o * (din + 1));
-    double s = 0.0;
-    if (i < din) {
-        for (int64_t r = 0; r < n; ++r) s += (double)dZ[r * dout + o] * (double)A[r * din + i];
-        dW[(int64_t)o * din + i] = (float)s;
-    } else {
-        for (int64_t r = 0; r < n; ++r) s += (double)dZ[r * dout + o];
-        db[o] = (float)s;
-    }
-}
+struct AdamArgs {
+    float lr, b1, b2, eps, c1, c2;
+};
 
-__global__ void k_adam(float* p, const float* g, float* m, float* v, int64_t P, float lr, float b1, float b2,
-                       float eps, float c1, float c2) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= P) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
+__device__ __forceinline__ void adam_update(float* p, float gi, float* m, float* v, int64_t i, const AdamArgs& a) {
+    const float mi = a.b1 * m[i] + (1.0f - a.b1) * gi;
+    const float vi = a.b2 * v[i] + (1.0f - a.b2) * gi * gi;
     m[i] = mi;
     v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    p[i] -= a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+}
+
+__global__ void k_adam(float* p, const float* g, float* m, float* v, int64_t P, AdamArgs a) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < P) adam_update(p, g[i], m, v, i, a);
 }
 
 __global__ void k_log_targets(const double* x, float* t, int64_t n, double floor_v) {
@@ -243,57 +248,472 @@ __global__ void k_log_targets(const double* x, float* t, int64_t n, double floor
 
 static unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
-// forward through all layers; activations kept in the workspace
-static void forward(const MlpLayout& L, const float* state, const float* x, int64_t n, float* ws, hipStream_t s,
-                    float** out_y) {
-    float* xn = ws;
-    float* acts = xn + n * L.n_in;
-    float* y = acts + (int64_t)L.depth * n * L.width;
+static AdamArgs adam_args(float lr, int step) {
+    AdamArgs a{lr, 0.9f, 0.999f, 1e-8f, 0, 0};
+    a.c1 = 1.0f - std::pow(a.b1, (float)step);
+    a.c2 = 1.0f - std::pow(a.b2, (float)step);
+    return a;
+}
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4f_u __attribute__((ext_vector_type(4), aligned(4)));   // 4 floats at any float's alignment
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// ---------------------------------------------------------------------------
+// The whole network of a block of 16 RT rows in one launch: normalized rows
+// and activations stay in LDS, eight waves take 16 CT output columns each, and
+// the products run on the FP32 matrix cores (v_mfma_f32_16x16x4f32).  A lane
+// takes four consecutive inner indices of its row (LDS) and of its weight row
+// (global, one 16-byte load), so instruction j of a group of 16 inner indices
+// multiplies indices kb + 4 (lane / 16) + j.
+//   TRAIN = false: the output column only, layers in place in one LDS buffer.
+//   TRAIN = true: also the loss partial of the block, dL/dy, and the gradients
+//     through the layers (the same products against W instead of W^T), each
+//     written over its layer's activations in LDS; normalized rows,
+//     activations and gradients go to the workspace for the weight gradients.
+// Bound: the matrix cores for many rows; for a mini-batch (4096 rows: 256
+// blocks, one per CU) the chain of 2 depth layers, each its weights from L2
+// (150 KB per block at 36 -> 128 x 3 -> 1) and its MFMAs.  36 -> 128 x 3 -> 1:
+// scores of 32490 rows 112 us with a launch per layer (64 x 64 FMA tiles), 31 us
+// with this one; the training step below.
+// ---------------------------------------------------------------------------
+struct MlpArgs {
+    const float *x, *t, *w, *mean, *istd, *params;
+    float *y, *xn, *acts, *dy, *dz;
+    double* part;
+    int64_t n;
+    int n_in, width, depth, pitch;
+};
+
+template <int RT, int CT, bool TRAIN>
+__global__ __launch_bounds__(512) void k_mlp_fused(MlpArgs a) {
+    constexpr int R = 16 * RT;
+    extern __shared__ __align__(16) float lds[];
+    __shared__ float dys[R];
+    __shared__ double ls[R];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int sub = lane & 15, grp = lane >> 4;
+    const int pitch = a.pitch, W = a.width, D = a.n_in;
+    const int64_t r0 = (int64_t)blockIdx.x * R;
+    const int64_t bufsz = (int64_t)R * pitch;
+    const int64_t lsz = (int64_t)W * W + W;                  // parameters of a hidden layer past the first
+    const float* p1 = a.params + (int64_t)D * W + W;         // second layer
+    // rows in, normalized; inner columns up to a multiple of 16 are zero
+    const int din16 = (D + 15) & ~15, w16 = (W + 15) & ~15;
+    for (int e = tid; e < R * din16; e += 512) {
+        const int r = e / din16, c = e - r * din16;
+        float v = 0.0f;
+        if (c < D && r0 + r < a.n) {
+            v = (a.x[(r0 + r) * D + c] - a.mean[c]) * a.istd[c];
+            if (TRAIN) a.xn[(r0 + r) * D + c] = v;
+        }
+        lds[r * pitch + c] = v;
+    }
+    __syncthreads();
+    const int c0 = wave * 16 * CT;                           // this wave's first column
+    v4f acc[RT][CT];
+    // acc = In Wt^T (bwd = false: Wt is W x K, lane's column is a row of it) or
+    // In Wt (bwd = true: Wt is K x W), K <= 256 inner indices in groups of 16
+    auto product = [&](const float* in, const float* Wt, int K, auto bwd) {
+        constexpr bool BWD = decltype(bwd)::value;
+        constexpr int G = 8;                                 // groups whose weights are loaded ahead
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int j = 0; j < CT; ++j) acc[i][j] = v4f{0, 0, 0, 0};
+        const int ng = (K + 15) >> 4;
+        for (int g0 = 0; g0 < ng; g0 += G) {
+            v4f w[CT][G];
+#pragma unroll
+            for (int j = 0; j < CT; ++j) {
+                const int col = c0 + 16 * j + sub;
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const int k = 16 * (g0 + g) + 4 * grp;
+                    w[j][g] = v4f{0, 0, 0, 0};
+                    if (col >= W || k >= K) continue;
+                    if constexpr (BWD) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if (k + q < K) w[j][g][q] = Wt[(int64_t)(k + q) * W + col];
+                    } else {
+                        const float* p = Wt + (int64_t)col * K + k;
+                        if (k + 3 < K) {
+                            w[j][g] = *(const v4f_u*)p;
+                        } else {
+#pragma unroll
+                            for (int q = 0; q < 3; ++q)
+                                if (k + q < K) w[j][g][q] = p[q];
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                if (g0 + g >= ng) break;
+                v4f x[RT];
+#pragma unroll
+                for (int i = 0; i < RT; ++i)
+                    x[i] = *(const v4f*)&in[(16 * i + sub) * pitch + 16 * (g0 + g) + 4 * grp];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int i = 0; i < RT; ++i)
+#pragma unroll
+                        for (int j = 0; j < CT; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i][q], w[j][g][q], acc[i][j], 0, 0, 0);
+            }
+        }
+    };
+    // element e of a lane's result is row 4 grp + e of its block
+    float* cur = lds;
+    for (int l = 0; l < a.depth; ++l) {
+        const float* Wl = l == 0 ? a.params : p1 + (l - 1) * lsz;
+        const int K = l == 0 ? D : W;
+        const float* bl = Wl + (int64_t)K * W;
+        if (c0 < w16) product(cur, Wl, K, std::integral_constant<bool, false>{});
+        float* nxt = TRAIN ? cur + bufsz : cur;
+        if (!TRAIN) __syncthreads();                         // every wave has read the rows it overwrites
+        if (c0 < w16) {
+#pragma unroll
+            for (int j = 0; j < CT; ++j) {
+                const int col = c0 + 16 * j + sub;
+                if (col >= w16) continue;
+                const float bias = col < W ? bl[col] : 0.0f;
+#pragma unroll
+                for (int i = 0; i < RT; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int r = 16 * i + 4 * grp + e;
+                        const float s = acc[i][j][e] + bias;
+                        const float v = col < W && s > 0.0f ? s : 0.0f;
+                        nxt[r * pitch + col] = v;
+                        if (TRAIN && col < W && r0 + r < a.n)
+                            a.acts[((int64_t)l * a.n + r0 + r) * W + col] = v;
+                    }
+            }
+        }
+        cur = nxt;
+        __syncthreads();
+    }
+    // output layer: 512 / R threads per row, fixed-order butterfly
+    const float* Wo = p1 + (int64_t)(a.depth - 1) * lsz;
+    constexpr int T = 512 / R;
+    {
+        const int r = tid / T, q = tid % T;
+        float s = 0.0f;
+        for (int c = q; c < W; c += T) s = fmaf(cur[r * pitch + c], Wo[c], s);
+#pragma unroll
+        for (int off = T / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
+        const float y = s + Wo[W];
+        if (q == 0) {
+            const int64_t row = r0 + r;
+            if (!TRAIN) {
+                if (row < a.n) a.y[row] = y;
+            } else {
+                float dy = 0.0f;
+                double l = 0.0;
+                if (row < a.n) {
+                    const float wi = a.w ? a.w[row] : 1.0f;
+                    const float d = y - a.t[row];
+                    dy = 2.0f * wi * d / (float)a.n;
+                    l = (double)wi * (double)d * (double)d;
+                    a.dy[row] = dy;
+                }
+                dys[r] = dy;
+                ls[r] = l;
+            }
+        }
+    }
+    if constexpr (TRAIN) {
+        __syncthreads();
+        if (tid == 0) {
+            double l = 0.0;
+            for (int r = 0; r < R; ++r) l += ls[r];
+            a.part[blockIdx.x] = l;
+        }
+        // gradient of the last hidden layer's pre-activations, over its activations
+        for (int e = tid; e < R * w16; e += 512) {
+            const int r = e / w16, c = e - r * w16;
+            float g = 0.0f;
+            if (c < W && cur[r * pitch + c] > 0.0f) g = dys[r] * Wo[c];
+            cur[r * pitch + c] = g;
+            if (c < W && r0 + r < a.n) a.dz[((int64_t)(a.depth - 1) * a.n + r0 + r) * W + c] = g;
+        }
+        __syncthreads();
+        for (int l = a.depth - 1; l > 0; --l) {
+            float* prev = cur - bufsz;                       // activations below layer l, then their gradients
+            if (c0 < w16) {
+                product(cur, p1 + (l - 1) * lsz, W, std::integral_constant<bool, true>{});
+#pragma unroll
+                for (int j = 0; j < CT; ++j) {
+                    const int col = c0 + 16 * j + sub;
+                    if (col >= w16) continue;
+#pragma unroll
+                    for (int i = 0; i < RT; ++i)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int r = 16 * i + 4 * grp + e;
+                            const float g = prev[r * pitch + col] > 0.0f ? acc[i][j][e] : 0.0f;
+                            prev[r * pitch + col] = g;
+                            if (col < W && r0 + r < a.n) a.dz[((int64_t)(l - 1) * a.n + r0 + r) * W + col] = g;
+                        }
+                }
+            }
+            cur = prev;
+            __syncthreads();
+        }
+    }
+}
+
+// Weight and bias gradients of layers [l0, l0 + count): dW[o][i] =
+// sum_r dZ[r][o] A[r][i], db[o] = sum_r dZ[r][o], accumulated in FP64 on the
+// matrix cores (v_mfma_f64_16x16x4f64; products of two floats are exact).
+// Block (tile, split): 64 x 64 weights over one range of rows, a wave 32 x 32
+// of them read straight from the row-major operands (64-byte runs).  Bound: the
+// row range's loads.  A training step of 4096 rows, 36 -> 128 x 3 -> 1: 6137 us
+// with one thread per weight summing all rows, 54 us with this launch and the
+// fused one (three launches instead of 15).
+struct GradLayer {
+    const float *dz, *act;
+    int64_t w_off, b_off;
+    int dout, din, tile0;          // first tile of the layer
+};
+struct GradArgs {
+    GradLayer layer[17];
+    int n_layers, splits;
+    int64_t n, rows, P;            // rows: rows of a split
+    float* grads;                  // splits == 1: written here
+    double* part;                  // else: partials [split][P]
+};
+
+__global__ __launch_bounds__(256) void k_mlp_wgrad(GradArgs a) {
+    int l = 0;
+    while (l + 1 < a.n_layers && (int)blockIdx.x >= a.layer[l + 1].tile0) ++l;
+    const GradLayer& L = a.layer[l];
+    const int t = (int)blockIdx.x - L.tile0;
+    const int ti_n = (L.din + kGradTile - 1) / kGradTile;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int o0 = t / ti_n * kGradTile + 32 * (wave >> 1), i0 = t % ti_n * kGradTile + 32 * (wave & 1);
+    if (o0 >= L.dout || i0 >= L.din) return;
+    const int sub = lane & 15, grp = lane >> 4;
+    const int64_t rb = (int64_t)blockIdx.y * a.rows;
+    const int64_t re = rb + a.rows < a.n ? rb + a.rows : a.n;
+    const float* __restrict__ dz = L.dz;
+    const float* __restrict__ act = L.act;
+    const bool ov[2] = {o0 + sub < L.dout, o0 + 16 + sub < L.dout};
+    const bool iv[2] = {i0 + sub < L.din, i0 + 16 + sub < L.din};
+    const bool two_o = o0 + 16 < L.dout, two_i = i0 + 16 < L.din;
+    v4d acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = v4d{0, 0, 0, 0};
+    double bs[2] = {0.0, 0.0};
+    constexpr int U = 8;           // row groups of 4 whose loads are in flight together
+    for (int64_t r = rb; r < re; r += 4 * U) {
+        float x[U][2], y[U][2];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t row = r + 4 * u + grp;
+            const bool rv = row < re;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                x[u][q] = rv && ov[q] ? dz[row * L.dout + o0 + 16 * q + sub] : 0.0f;
+                y[u][q] = rv && iv[q] ? act[row * L.din + i0 + 16 * q + sub] : 0.0f;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double xd[2] = {(double)x[u][0], (double)x[u][1]}, yd[2] = {(double)y[u][0], (double)y[u][1]};
+            bs[0] += xd[0];
+            bs[1] += xd[1];
+            acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(xd[0], yd[0], acc[0][0], 0, 0, 0);
+            if (two_i) acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(xd[0], yd[1], acc[0][1], 0, 0, 0);
+            if (two_o) acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(xd[1], yd[0], acc[1][0], 0, 0, 0);
+            if (two_o && two_i) acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(xd[1], yd[1], acc[1][1], 0, 0, 0);
+        }
+    }
+    double* part = a.part + (int64_t)blockIdx.y * a.P;
+    auto put = [&](int64_t at, double v) {
+        if (a.splits == 1) a.grads[at] = (float)v;
+        else part[at] = v;
+    };
+    // element e of a lane's result is row grp + 4 e of its block
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int o = o0 + 16 * i + grp + 4 * e;
+                if (o < L.dout && iv[j]) put(L.w_off + (int64_t)o * L.din + i0 + 16 * j + sub, acc[i][j][e]);
+            }
+    if (i0 == 0) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            bs[i] += __shfl_xor(bs[i], 16);
+            bs[i] += __shfl_xor(bs[i], 32);
+            if (grp == 0 && ov[i]) put(L.b_off + o0 + 16 * i + sub, bs[i]);
+        }
+    }
+}
+
+// Gradient partials added in range order, the Adam update of the same weight
+// (adam != 0), and the loss (the launch's last block).
+__global__ __launch_bounds__(256) void k_mlp_reduce(const double* part, int splits, int64_t P, float* g, float* p,
+                                                    float* m, float* v, int adam, AdamArgs aa, const double* lpart,
+                                                    int nb, int64_t n, float* loss) {
+    if (blockIdx.x == gridDim.x - 1) {
+        __shared__ double red[256];
+        double s = 0;
+        for (int i = threadIdx.x; i < nb; i += 256) s += lpart[i];
+        red[threadIdx.x] = s;
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) *loss = (float)(red[0] / (double)n);
+        return;
+    }
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= P) return;
+    float gi;
+    if (splits > 1) {
+        double s = 0.0;
+#pragma unroll 8
+        for (int q = 0; q < splits; ++q) s += part[q * P + i];
+        gi = (float)s;
+        g[i] = gi;
+    } else {
+        gi = g[i];
+    }
+    if (adam) adam_update(p, gi, m, v, i, aa);
+}
+
+// The fused launch serves networks whose layers a block's eight waves hold in
+// registers (up to 256 columns) and whose rows fit 64 KB of LDS; others go
+// layer by layer.  Rows per block: 64 for the most reuse of a block's weight
+// reads, fewer while that leaves CUs without a block.  Returns the LDS bytes of
+// a block of 16 rt rows, 0 if the shape is not served.
+static size_t fused_lds(const MlpLayout& L, int rt, bool train, int* pitch) {
+    const int cols = (std::max(L.n_in, L.width) + 15) / 16 * 16;
+    *pitch = cols + 4;      // rows start 4 LDS banks apart: conflict-free 16-byte reads
+    const size_t b = (size_t)16 * rt * *pitch * 4 * (train ? L.depth + 1 : 1);
+    return cols <= 256 && b <= 60 * 1024 ? b : 0;
+}
+
+template <int RT, bool TRAIN>
+static void launch_fused_rt(const MlpArgs& a, size_t lds, hipStream_t s) {
+    const dim3 grid(nblk(a.n, 16 * RT));
+    if (a.width <= 128) hipLaunchKernelGGL((k_mlp_fused<RT, 1, TRAIN>), grid, dim3(512), lds, s, a);
+    else hipLaunchKernelGGL((k_mlp_fused<RT, 2, TRAIN>), grid, dim3(512), lds, s, a);
+}
+
+// launches the fused kernel; returns its row blocks, 0 if the shape is not served
+template <bool TRAIN>
+static int64_t launch_fused(const MlpLayout& L, MlpArgs a, hipStream_t s) {
+    int rt = TRAIN ? 2 : 4;
+    while (rt > 1 && (a.n < (int64_t)16 * rt * 256 || !fused_lds(L, rt, TRAIN, &a.pitch))) rt /= 2;
+    const size_t lds = fused_lds(L, rt, TRAIN, &a.pitch);
+    if (!lds) return 0;
+    if (rt == 1) launch_fused_rt<1, TRAIN>(a, lds, s);
+    else if (rt == 2) launch_fused_rt<2, TRAIN>(a, lds, s);
+    else if constexpr (!TRAIN) launch_fused_rt<4, TRAIN>(a, lds, s);
+    return nblk(a.n, 16 * rt);
+}
+
+static MlpArgs mlp_args(const MlpLayout& L, const float* state, const float* x, int64_t n) {
+    MlpArgs a{};
+    a.x = x;
+    a.mean = state + L.norm_off;
+    a.istd = a.mean + L.n_in;
+    a.params = state + L.params_off;
+    a.n = n;
+    a.n_in = L.n_in;
+    a.width = L.width;
+    a.depth = L.depth;
+    return a;
+}
+
+// layer by layer, activations kept in the workspace
+static void forward_layers(const MlpLayout& L, const float* state, const float* x, int64_t n, float* ws, float* y,
+                           hipStream_t s) {
+    const MlpWs o = ws_layout(L, n);
     hipLaunchKernelGGL(k_normalize, dim3(nblk(n * L.n_in, 256)), dim3(256), 0, s, x, state + L.norm_off,
-                       state + L.norm_off + L.n_in, xn, n, L.n_in);
-    const float* in = xn;
+                       state + L.norm_off + L.n_in, ws + o.xn, n, L.n_in);
+    const float* in = ws + o.xn;
     const float* params = state + L.params_off;
     for (int l = 0; l < L.n_layers; ++l) {
         const bool last = l == L.n_layers - 1;
-        float* out = last ? y : acts + (int64_t)l * n * L.width;
+        float* out = last ? y : ws + o.acts + (int64_t)l * n * L.width;
         dim3 grid(nblk(n, 64), nblk(L.dout[l], 64));
         hipLaunchKernelGGL(k_linear_fwd, grid, dim3(256), 0, s, in, params + L.w_off[l], params + L.b_off[l], out, n,
                            L.din[l], L.dout[l], last ? 0 : 1);
         in = out;
     }
-    *out_y = y;
 }
 
+static void forward(const MlpLayout& L, const float* state, const float* x, int64_t n, float* ws, float* y,
+                    hipStream_t s) {
+    MlpArgs a = mlp_args(L, state, x, n);
+    a.y = y;
+    if (!launch_fused<false>(L, a, s)) forward_layers(L, state, x, n, ws, y, s);
+}
+
+// loss and gradients, and with `adam` the update of the parameters
 static void gradients(const MlpLayout& L, float* state, const float* x, const float* t, const float* w, int64_t n,
-                      float* ws, float* loss, hipStream_t s) {
-    float* y = nullptr;
-    forward(L, state, x, n, ws, s, &y);
-    float* xn = ws;
-    float* acts = xn + n * L.n_in;
-    float* g0 = y + n;
-    float* g1 = g0 + n * std::max(L.width, L.n_in);
-    // FP64 partials start on a 256-byte boundary (the float regions before
-    // them can have odd length)
-    const int64_t part_off = ((g1 - ws) + n * std::max(L.width, L.n_in) + 63) / 64 * 64;
-    double* part = (double*)(ws + part_off);
-    const unsigned nb = nblk(n, 256);
-    hipLaunchKernelGGL(k_loss_grad, dim3(nb), dim3(256), 0, s, y, t, w, g0, part, n);
-    hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(256), 0, s, part, (int)nb, n, loss);
+                      float* ws, float* loss, const AdamArgs* adam, hipStream_t s) {
+    const MlpWs o = ws_layout(L, n);
+    double* lpart = (double*)(ws + o.part);
     float* params = state + L.params_off;
-    float* grads = state + L.grads_off;
-    float* dz = g0;     // gradient w.r.t. the current layer's pre-activation
-    float* other = g1;
-    for (int l = L.n_layers - 1; l >= 0; --l) {
-        const float* a_prev = l == 0 ? xn : acts + (int64_t)(l - 1) * n * L.width;
-        const int64_t nw = (int64_t)L.dout[l] * (L.din[l] + 1);
-        hipLaunchKernelGGL(k_linear_bwd_weight, dim3(nblk(nw, 256)), dim3(256), 0, s, dz, a_prev,
-                           grads + L.w_off[l], grads + L.b_off[l], n, L.din[l], L.dout[l]);
-        if (l > 0) {
+    MlpArgs a = mlp_args(L, state, x, n);
+    a.t = t;
+    a.w = w;
+    a.xn = ws + o.xn;
+    a.acts = ws + o.acts;
+    a.dy = ws + o.dy;
+    a.dz = ws + o.dz;
+    a.part = lpart;
+    int64_t nb = launch_fused<true>(L, a, s);
+    if (!nb) {
+        forward_layers(L, state, x, n, ws, ws + o.y, s);
+        nb = nblk(n, 256);
+        hipLaunchKernelGGL(k_loss_grad, dim3((unsigned)nb), dim3(256), 0, s, ws + o.y, t, w, a.dy, lpart, n);
+        const float* dz = a.dy;
+        for (int l = L.n_layers - 1; l > 0; --l) {
+            float* below = a.dz + (int64_t)(l - 1) * n * L.width;
             hipLaunchKernelGGL(k_linear_bwd_data, dim3(nblk(n * L.din[l], 256)), dim3(256), 0, s, dz,
-                               params + L.w_off[l], a_prev, other, n, L.din[l], L.dout[l]);
-            std::swap(dz, other);
+                               params + L.w_off[l], a.acts + (int64_t)(l - 1) * n * L.width, below, n, L.din[l],
+                               L.dout[l]);
+            dz = below;
         }
     }
+    GradArgs g{};
+    g.n_layers = L.n_layers;
+    g.splits = (int)grad_splits(L, n);
+    g.n = n;
+    g.rows = (n + g.splits - 1) / g.splits;
+    g.P = L.P;
+    g.grads = state + L.grads_off;
+    g.part = (double*)(ws + o.grad);
+    int tiles = 0;
+    for (int l = 0; l < L.n_layers; ++l) {
+        GradLayer& q = g.layer[l];
+        q.dz = l == L.depth ? a.dy : a.dz + (int64_t)l * n * L.width;
+        q.act = l == 0 ? a.xn : a.acts + (int64_t)(l - 1) * n * L.width;
+        q.w_off = L.w_off[l];
+        q.b_off = L.b_off[l];
+        q.dout = L.dout[l];
+        q.din = L.din[l];
+        q.tile0 = tiles;
+        tiles += ((q.dout + kGradTile - 1) / kGradTile) * ((q.din + kGradTile - 1) / kGradTile);
+    }
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)tiles, (unsigned)g.splits), dim3(256), 0, s, g);
+    hipLaunchKernelGGL(k_mlp_reduce, dim3(nblk(L.P, 256) + 1), dim3(256), 0, s, g.part, g.splits, L.P, g.grads,
+                       params, state + L.m_off, state + L.v_off, adam ? 1 : 0, adam ? *adam : AdamArgs{}, lpart,
+                       (int)nb, n, loss);
 }
 
 }  // namespace tn
@@ -322,7 +742,7 @@ int tn_mlp_sizes(const tn_mlp_shape* s, int64_t batch, int64_t* n_params, size_t
         MlpLayout L = layout_of(s);
         if (n_params) *n_params = L.P;
         if (state_bytes) *state_bytes = (size_t)L.total * 4;
-        if (ws_bytes) *ws_bytes = (size_t)ws_floats(L, std::max<int64_t>(1, batch)) * 4 + 4096 * 8;
+        if (ws_bytes) *ws_bytes = (size_t)ws_layout(L, std::max<int64_t>(1, batch)).total * 4;
     });
 }
 
@@ -359,9 +779,7 @@ int tn_mlp_forward(const tn_mlp_shape* s, const void* d_state, const float* d_x,
     return mguard([&] {
         MlpLayout L = layout_of(s);
         if (!d_state || !d_x || !d_y || !d_ws || n < 1) fail(TN_EINVAL, "bad forward arguments");
-        float* y = nullptr;
-        forward(L, (const float*)d_state, d_x, n, (float*)d_ws, (hipStream_t)stream, &y);
-        HIPCHK_M(hipMemcpyAsync(d_y, y, n * 4, hipMemcpyDeviceToDevice, (hipStream_t)stream));
+        forward(L, (const float*)d_state, d_x, n, (float*)d_ws, d_y, (hipStream_t)stream);
         HIPCHK_M(hipGetLastError());
     });
 }
@@ -371,7 +789,7 @@ int tn_mlp_gradients(const tn_mlp_shape* s, void* d_state, const float* d_x, con
     return mguard([&] {
         MlpLayout L = layout_of(s);
         if (!d_state || !d_x || !d_t || !d_ws || !d_loss || n < 1) fail(TN_EINVAL, "bad gradient arguments");
-        gradients(L, (float*)d_state, d_x, d_t, d_w, n, (float*)d_ws, d_loss, (hipStream_t)stream);
+        gradients(L, (float*)d_state, d_x, d_t, d_w, n, (float*)d_ws, d_loss, nullptr, (hipStream_t)stream);
         HIPCHK_M(hipGetLastError());
     });
 }
@@ -380,11 +798,9 @@ int tn_mlp_adam(const tn_mlp_shape* s, void* d_state, float lr, int32_t step, vo
     return mguard([&] {
         MlpLayout L = layout_of(s);
         if (!d_state || step < 1) fail(TN_EINVAL, "bad adam arguments");
-        const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-        const float c1 = 1.0f - std::pow(b1, (float)step), c2 = 1.0f - std::pow(b2, (float)step);
         float* st = (float*)d_state;
         hipLaunchKernelGGL(k_adam, dim3(nblk(L.P, 256)), dim3(256), 0, (hipStream_t)stream, st + L.params_off,
-                           st + L.grads_off, st + L.m_off, st + L.v_off, L.P, lr, b1, b2, eps, c1, c2);
+                           st + L.grads_off, st + L.m_off, st + L.v_off, L.P, adam_args(lr, step));
         HIPCHK_M(hipGetLastError());
     });
 }
@@ -400,9 +816,16 @@ int tn_mlp_log_targets(const double* d_x, float* d_t, int64_t n, double floor_v,
 
 int tn_mlp_train_step(const tn_mlp_shape* s, void* d_state, const float* d_x, const float* d_t, const float* d_w,
                       int64_t n, float lr, int32_t step, void* d_ws, float* d_loss, void* stream) {
-    int rc = tn_mlp_gradients(s, d_state, d_x, d_t, d_w, n, d_ws, d_loss, stream);
-    if (rc != TN_OK) return rc;
-    return tn_mlp_adam(s, d_state, lr, step, stream);
+    return mguard([&] {
+        MlpLayout L = layout_of(s);
+        if (!d_state || !d_x || !d_t || !d_ws || !d_loss || n < 1) fail(TN_EINVAL, "bad gradient arguments");
+        // as two calls: with a bad step the gradients are still computed
+        const AdamArgs a = adam_args(lr, std::max(step, 1));
+        gradients(L, (float*)d_state, d_x, d_t, d_w, n, (float*)d_ws, d_loss, step < 1 ? nullptr : &a,
+                  (hipStream_t)stream);
+        HIPCHK_M(hipGetLastError());
+        if (step < 1) fail(TN_EINVAL, "bad adam arguments");
+    });
 }
 
 int tn_pruner_train_step(const tn_mlp_shape* s, void* d_state, const float* d_x, const float* d_t,
