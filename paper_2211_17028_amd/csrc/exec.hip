@@ -89,16 +89,43 @@ struct Arena {
     }
 };
 
-// constants staged on the host and uploaded in one copy
+// Constants staged on the host and uploaded to the start of the workspace in
+// one copy.  Buffers that the device writes before it reads them (values of
+// slot-free subtrees, cluster roots, per-term outputs) lie behind the data and
+// are not uploaded: a 25-qubit amplitude batch has 35 MB of constants, 0.5 MB of
+// them data (its call took 1832 us with all of it uploaded, 1260 us without).
+// While a schedule is built their offsets are marked; place() gives the offset
+// in the region once finish() has fixed the data's size.
 struct ConstBuf {
     std::vector<unsigned char> bytes;
+    static constexpr int64_t kZeroed = int64_t(1) << 60, kOutput = int64_t(1) << 61;
+    int64_t data_bytes = 0, zeroed_bytes = 0, output_bytes = 0;
     int64_t add(const void* p, int64_t n) {
-        int64_t off = round_up((int64_t)bytes.size(), 256);
+        int64_t off = round_up((int64_t)bytes.size(), 32);   // the widest loads
         bytes.resize(off + n);
         if (p) std::memcpy(bytes.data() + off, p, n);
         return off;
     }
     int64_t reserve(int64_t n) { return add(nullptr, n); }
+    // a buffer the device writes; zeroed: zero until then (per-term outputs,
+    // which a caller can read before the first run)
+    int64_t reserve_output(int64_t n, bool zeroed = false) {
+        int64_t& end = zeroed ? zeroed_bytes : output_bytes;
+        const int64_t off = end;
+        end += round_up(n, 256);
+        return off | (zeroed ? kZeroed : kOutput);
+    }
+    void finish() {
+        data_bytes = round_up((int64_t)bytes.size(), 256);
+        bytes.resize(data_bytes + zeroed_bytes + output_bytes);
+    }
+    int64_t place(int64_t off) const {
+        if (off & kZeroed) return data_bytes + (off & ~kZeroed);
+        if (off & kOutput) return data_bytes + zeroed_bytes + (off & ~kOutput);
+        return off;
+    }
+    // first: the workspace has not held this region before
+    size_t upload_bytes(bool first) const { return (size_t)(data_bytes + (first ? zeroed_bytes : 0)); }
 };
 
 // R_WORK2: the FP64 pass (side stream); R_HOST: pinned host memory the tail
@@ -350,10 +377,97 @@ struct GroupJob {
     Ref a, b, c, oa, ob;
     int fp64 = 0;              // complex128 job (dominant-term pass) in a launch of either precision
     int64_t n_inst = 0;
-    int m_log = 0, n_log = 0, k_log = 0, split = 0, rpt_log = 0;
+    int m_log = 0, n_log = 0, k_log = 0, split = 0;
+    int rl = 0, cl = 0;        // log2 rows and columns of a thread (split: of a block)
+    Ref koff, steps;           // offsets inside a chunk (chunks of over 8; shorter ones are in the record)
     int8_t a_row[32] = {}, a_k[32] = {}, b_k[32] = {}, b_col[32] = {};
     double flops = 0, bytes = 0;
 };
+
+static int64_t job_blocks(const GroupJob& j) {
+    const int64_t units = j.n_inst << (j.m_log + j.n_log - j.rl - j.cl);
+    return j.split ? units : (units + 255) / 256;
+}
+
+// Outputs per thread (per block with split sums) of a small step.
+static void gett_shape(GroupJob& j) {
+    const int64_t outs = j.n_inst << (j.m_log + j.n_log);
+    if (j.split) {
+        // Every element of a row or column is read once per block that needs
+        // it: the largest tile of outputs that still leaves a block per CU (the
+        // 36-qubit QAOA's 1446 slices of 4 x 2 over 8192 terms, a block per
+        // output: 1.5 GB of reads, 207 us; a block per slice: 82 us).
+        // FP64 holds 4 outputs and their loads in registers, FP32 16.
+        static const int shapes[][2] = {{2, 2}, {2, 1}, {1, 2}, {1, 1}, {1, 0}, {0, 1}};
+        for (const auto& q : shapes) {
+            if (q[0] > j.m_log || q[1] > j.n_log || (j.fp64 && q[0] + q[1] > 2)) continue;
+            if ((outs >> (q[0] + q[1])) < kNumCUs) continue;
+            j.rl = q[0];
+            j.cl = q[1];
+            return;
+        }
+        return;
+    }
+    // at least 64K threads stay busy; FP32 columns that are adjacent in the
+    // column operand come in pairs (16-byte loads and stores), then rows (the
+    // column operand's elements are reused across them; none for outer
+    // products, where there is no reuse), then two pairs of columns where a
+    // block's outputs are one row group (k_gett_group's scalar row loads)
+    int t = 0;
+    while (t < 4 && (outs >> (t + 1)) >= (int64_t(1) << 16)) ++t;
+    int adj = 0;
+    while (!j.fp64 && adj < 2 && adj < j.n_log && j.b_col[adj] == adj) ++adj;
+    j.cl = std::min(t, std::min(adj, 1));
+    j.rl = j.k_log == 0 ? 0 : std::min(std::min(j.m_log, t - j.cl), j.cl ? 2 : 3);
+    if (j.cl == 1 && adj == 2 && t > j.rl + 1 && j.n_log >= 10) j.cl = 2;
+}
+
+static int64_t place_bits(int64_t x, const int8_t* pos, int n) {
+    int64_t o = 0;
+    for (int q = 0; q < n; ++q)
+        if ((x >> q) & 1) o += int64_t(1) << pos[q];
+    return o;
+}
+
+// log2 of a small step's chunk of inner indices: 256, or fewer where an offset
+// inside the chunk would pass 32 bits
+static int kc_log_of(const GroupJob& j) {
+    int q = 0;
+    while (q < j.k_log && q < 8 && j.a_k[q] < 32 && j.b_k[q] < 32) ++q;
+    return q;
+}
+
+static std::vector<GettOff> gett_offsets(const GroupJob& j) {
+    const int kc_log = kc_log_of(j);
+    std::vector<GettOff> t;
+    for (int64_t p = 0; p < (int64_t(1) << kc_log); ++p)
+        t.push_back({(uint32_t)place_bits(p, j.a_k, kc_log), (uint32_t)place_bits(p, j.b_k, kc_log)});
+    return t;
+}
+
+// offset steps between chunks (entry t: from a chunk index with t low ones to the next)
+static std::vector<GettStep> gett_steps(const GroupJob& j) {
+    const int kc_log = kc_log_of(j), n = j.k_log - kc_log;
+    std::vector<GettStep> t;
+    for (int q = 0; q < n; ++q) {
+        const int64_t below = (int64_t(1) << q) - 1, at = int64_t(1) << q;
+        t.push_back({place_bits(at, j.a_k + kc_log, n) - place_bits(below, j.a_k + kc_log, n),
+                     place_bits(at, j.b_k + kc_log, n) - place_bits(below, j.b_k + kc_log, n)});
+    }
+    return t;
+}
+
+// stored positions as runs of adjacent bits
+static int bit_runs(const int8_t* pos, int n, uint32_t* runs) {
+    int r = 0;
+    for (int q = 0; q < n;) {
+        int e = q + 1;
+        while (e < n && pos[e] == pos[e - 1] + 1) ++e;
+        runs[r++] = (uint32_t)q | (uint32_t)(e - q - 1) << 8 | (uint32_t)(uint8_t)pos[q] << 16;
+        q = e;
+    }
+    return r;
+}
 
 // One grouped matrix-core contraction (host side of an MfmaJob).
 struct MJob {
@@ -861,7 +975,7 @@ struct Builder {
                 }
                 if (folded_out && !sr.has_fixed) {
                     sr.has_fixed = true;
-                    sr.c_fixed = Ref{R_CONST, ex->cbuf.reserve(sr.c_bytes)};
+                    sr.c_fixed = Ref{R_CONST, ex->cbuf.reserve_output(sr.c_bytes)};
                 }
                 (fp64 ? const64 : const32)->push_back(std::move(sr));
             };
@@ -1088,18 +1202,22 @@ struct Builder {
                 jb.k_log = rk;
                 jb.n_inst = ninst * nbatch;
                 jb.split = split_sum ? 1 : 0;
-                // rows per thread: the column operand's elements are reused across
-                // them (up to 8; 1 for outer products, where there is no reuse)
-                jb.rpt_log = jb.split || rk == 0 ? 0 : std::min(jb.m_log, 3);
-                // ... but keep at least 64K threads busy
-                while (jb.rpt_log > 0 && ((jb.n_inst << (jb.m_log + jb.n_log)) >> jb.rpt_log) < (int64_t(1) << 16))
-                    --jb.rpt_log;
                 for (size_t q = 0; q < row_bits.size(); ++q) jb.a_row[q] = (int8_t)posin(R, row_bits[q]);
                 for (size_t q = 0; q < k_bits.size(); ++q) {
                     jb.a_k[q] = (int8_t)posin(R, k_bits[q]);
                     jb.b_k[q] = (int8_t)posin(Q, k_bits[q]);
                 }
                 for (size_t q = 0; q < col_bits.size(); ++q) jb.b_col[q] = (int8_t)posin(Q, col_bits[q]);
+                if (kc_log_of(jb) < 8) jb.split = 0;
+                gett_shape(jb);
+                if (kc_log_of(jb) > 3) {
+                    const std::vector<GettOff> t = gett_offsets(jb);
+                    jb.koff = Ref{R_CONST, ex->cbuf.add(t.data(), (int64_t)(t.size() * sizeof(GettOff)))};
+                }
+                if (kc_log_of(jb) < rk) {
+                    const std::vector<GettStep> t = gett_steps(jb);
+                    jb.steps = Ref{R_CONST, ex->cbuf.add(t.data(), (int64_t)(t.size() * sizeof(GettStep)))};
+                }
                 jb.oa = slice_offsets(R, bt_bits);
                 jb.ob = slice_offsets(Q, bt_bits);
                 const double mm = std::ldexp(1.0, jb.m_log), nnn = std::ldexp(1.0, jb.n_log),
@@ -1327,8 +1445,7 @@ struct Builder {
                 subst(jb.a);
                 subst(jb.b);
                 subst(jb.c);
-                const int64_t outs = jb.n_inst << (jb.m_log + jb.n_log);
-                G.blocks += jb.split ? outs : ((outs >> jb.rpt_log) + 255) / 256;
+                G.blocks += job_blocks(jb);
                 G.flops += jb.flops;
                 G.bytes += jb.bytes;
                 G.hjobs.push_back(jb);
@@ -1458,6 +1575,30 @@ static void merge_fp64_chain(tn_exec_s* ex) {
     ex->launches64.clear();
 }
 
+// Fixes the constant region's layout and gives every reference to one of the
+// buffers behind its data its offset.
+static void place_outputs(tn_exec_s* ex) {
+    ex->cbuf.finish();
+    auto fix = [&](Ref& r) {
+        if (r.region == R_CONST) r.off = ex->cbuf.place(r.off);
+    };
+    for (auto* list : {&ex->launches_const, &ex->launches, &ex->launches64, &ex->plain_launches, &ex->tail})
+        for (Launch& L : *list) {
+            for (Ref* r : {&L.a, &L.b, &L.c, &L.x_out, &L.amp_out}) fix(*r);
+            for (GroupJob& j : L.hjobs)
+                for (Ref* r : {&j.a, &j.b, &j.c}) fix(*r);
+            for (MJob& j : L.mjobs)
+                for (Ref* r : {&j.a, &j.b, &j.c}) fix(*r);
+        }
+    for (PlanExec& pe : ex->plans) {
+        fix(pe.x_out);
+        fix(pe.amp_out);
+        for (Ref& r : pe.root32) fix(r);
+        for (Ref& r : pe.root64) fix(r);
+    }
+    fix(ex->tail_part);
+}
+
 static void build_schedule(tn_exec_s* ex, int n, const tn_plan* plans, const tn_terms* terms,
                            const std::map<int, std::pair<int, double>>* level_tile = nullptr,
                            TermRange range = TermRange{}, const std::set<int>* small_levels = nullptr) {
@@ -1532,7 +1673,7 @@ static void build_schedule(tn_exec_s* ex, int n, const tn_plan* plans, const tn_
                 pe.root32_inst.push_back(1);
             } else {
                 // roots stay live until finalize: the root step writes outside the work arena
-                Ref keep{R_CONST, ex->cbuf.reserve((int64_t)keys.size() * 8)};
+                Ref keep{R_CONST, ex->cbuf.reserve_output((int64_t)keys.size() * 8)};
                 pe.root32.push_back(bw.build_cluster(P, cl, keys, 0, pi, nullptr, keep, &steps32));
                 pe.root32_inst.push_back((int64_t)keys.size());
             }
@@ -1576,8 +1717,8 @@ static void build_schedule(tn_exec_s* ex, int n, const tn_plan* plans, const tn_
         // finalize + level sums
         std::vector<double> what(T.n);
         for (int64_t t = 0; t < T.n; ++t) what[t] = std::ldexp(T.w[t], -P.n_noise);
-        pe.x_out = Ref{R_CONST, ex->cbuf.reserve(std::max<int64_t>(1, T.n) * 8)};
-        pe.amp_out = Ref{R_CONST, ex->cbuf.reserve(std::max<int64_t>(1, T.n) * 8)};
+        pe.x_out = Ref{R_CONST, ex->cbuf.reserve_output(std::max<int64_t>(1, T.n) * 8, true)};
+        pe.amp_out = Ref{R_CONST, ex->cbuf.reserve_output(std::max<int64_t>(1, T.n) * 8, true)};
         pe.sums = Ref{R_HOST, ex->results_bytes};
         pe.x0 = Ref{R_HOST, ex->results_bytes + (T.level + 1) * 16};
         ex->results_bytes += (T.level + 1) * 16 + 8;
@@ -1638,8 +1779,10 @@ static void build_schedule(tn_exec_s* ex, int n, const tn_plan* plans, const tn_
         ex->tail_levels = std::max(ex->tail_levels, pe.terms->level + 1);
     }
     ex->tail_jobs = Ref{R_CONST, ex->cbuf.reserve((int64_t)n * (int64_t)sizeof(TailJob))};
-    ex->tail_part = Ref{R_CONST, ex->cbuf.reserve(std::max<int64_t>(1, ex->tail_blocks) * 16 * (TN_MAX_LEVEL + 1))};
-    ex->const_bytes = round_up((int64_t)ex->cbuf.bytes.size(), 256);
+    ex->tail_part = Ref{R_CONST,
+                        ex->cbuf.reserve_output(std::max<int64_t>(1, ex->tail_blocks) * 16 * (TN_MAX_LEVEL + 1))};
+    place_outputs(ex);
+    ex->const_bytes = (int64_t)ex->cbuf.bytes.size();
     ex->work1_bytes = round_up(bw.work.peak, 256);
     ex->work_bytes = ex->work1_bytes + round_up(bw.work2.peak, 256);
 }
@@ -1686,12 +1829,18 @@ static void bind(tn_exec_s* ex) {
                 j.n_log = h.n_log;
                 j.k_log = h.k_log;
                 j.split = h.split;
-                j.rpt_log = h.rpt_log;
-                std::memcpy(j.a_row, h.a_row, 32);
-                std::memcpy(j.a_k, h.a_k, 32);
-                std::memcpy(j.b_k, h.b_k, 32);
-                std::memcpy(j.b_col, h.b_col, 32);
-                const int64_t nb = gett_job_blocks(j);
+                j.rl = h.rl;
+                j.cl = h.cl;
+                j.n_row_runs = bit_runs(h.a_row, h.m_log, j.row_runs);
+                j.n_col_runs = bit_runs(h.b_col, h.n_log, j.col_runs);
+                for (int q = 0; q < 1 << h.rl; ++q) j.rlo[q] = place_bits(q, h.a_row, h.rl);
+                for (int q = 0; q < 1 << h.cl; ++q) j.clo[q] = place_bits(q, h.b_col, h.cl);
+                j.kc_log = kc_log_of(h);
+                const std::vector<GettOff> off = gett_offsets(h);
+                for (size_t q = 0; q < off.size() && q < 8; ++q) j.k8[q] = off[q];
+                if (j.kc_log > 3) j.koff = (const GettOff*)resolve(ex, h.koff);
+                if (j.kc_log < h.k_log) j.steps = (const GettStep*)resolve(ex, h.steps);
+                const int64_t nb = job_blocks(h);
                 for (int64_t q = 0; q < nb; ++q) tab[b0 + q] = (int32_t)((uint32_t)i | (h.fp64 ? 0x80000000u : 0u));
                 b0 += nb;
                 std::memcpy(d + i, &j, sizeof(GettJob));
@@ -2143,7 +2292,7 @@ static std::string describe_exec(const tn_exec_s* ex) {
                    << "," << h.b.off << "],\"c\":[" << h.c.region << "," << h.c.off << "],\"oa\":[" << h.oa.region
                    << "," << h.oa.off << "],\"ob\":[" << h.ob.region << "," << h.ob.off << "],\"n_inst\":"
                    << h.n_inst << ",\"m_log\":" << h.m_log << ",\"n_log\":" << h.n_log << ",\"k_log\":" << h.k_log
-                   << ",\"split\":" << h.split << ",\"rpt_log\":" << h.rpt_log;
+                   << ",\"split\":" << h.split << ",\"rpt_log\":" << h.rl << ",\"cpt_log\":" << h.cl;
                 auto arr = [&](const char* nm, const int8_t* v, int n) {
                     os << ",\"" << nm << "\":[";
                     for (int q = 0; q < n; ++q) os << (q ? "," : "") << (int)v[q];
@@ -2536,7 +2685,7 @@ static void bind_exec(tn_exec_s* ex, void* d_ws, size_t ws_bytes, hipStream_t st
                     HIPCHK(hipEventCreate(&L.ev_a));
                     HIPCHK(hipEventCreate(&L.ev_b));
                 }
-    HIPCHK(hipMemcpyAsync(ex->base, ex->cbuf.bytes.data(), ex->cbuf.bytes.size(), hipMemcpyHostToDevice,
+    HIPCHK(hipMemcpyAsync(ex->base, ex->cbuf.bytes.data(), ex->cbuf.upload_bytes(true), hipMemcpyHostToDevice,
                           ex->stream));
     run_const(ex, ex->stream);
     if (ex->opts.tune) autotune(ex);
@@ -2585,7 +2734,7 @@ struct CachedExec {
     size_t ws_bytes = 0;
     int device = 0;
     std::unique_ptr<tn_exec_s> ex;
-    void* pinned = nullptr;             // page-locked copy of the constant region
+    void* pinned = nullptr;             // page-locked copy of the constants
     size_t pinned_bytes = 0;
     hipStream_t last_stream = nullptr;
     uint64_t last_use = 0;
@@ -2651,7 +2800,7 @@ static CachedExec* cache_insert(int kind, int n, const tn_plan* plans, const tn_
     ce->last_stream = s;
     bind_exec(ex.get(), d_ws, ws_bytes, s);
     ce->device = ex->device;
-    ce->pinned_bytes = ex->cbuf.bytes.size();
+    ce->pinned_bytes = ex->cbuf.upload_bytes(false);
     HIPCHK(hipHostMalloc(&ce->pinned, std::max<size_t>(1, ce->pinned_bytes), hipHostMallocDefault));
     std::memcpy(ce->pinned, ex->cbuf.bytes.data(), ce->pinned_bytes);
     ce->ex = std::move(ex);
@@ -3325,7 +3474,7 @@ int tn_estimate_noalloc(int32_t n, const tn_plan* plans, const tn_terms* terms, 
         // constants (every buffer that must hold something before the run),
         // the slot-free steps, then both chains and the tail on the caller's
         // stream, one after the other
-        HIPCHK(hipMemcpyAsync(base, ex->cbuf.bytes.data(), ex->cbuf.bytes.size(), hipMemcpyHostToDevice, s));
+        HIPCHK(hipMemcpyAsync(base, ex->cbuf.bytes.data(), ex->cbuf.upload_bytes(false), hipMemcpyHostToDevice, s));
         run_const(ex.get(), s);
         for (auto& L : ex->launches64) enqueue(ex.get(), L, s);
         for (auto& L : ex->launches) enqueue(ex.get(), L, s);

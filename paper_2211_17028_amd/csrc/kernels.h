@@ -56,26 +56,41 @@ struct PermArgs {
 // GemmArgs' gathered form (slice offsets oa / ob, per-bit stored positions).
 // C is written row-major per slice.  Jobs of one launch are independent (one
 // level of the contraction trees) and sorted by block0.
+struct GettOff {
+    uint32_t a, b;                 // offsets of an inner index in A and B (elements)
+};
+struct GettStep {
+    int64_t a, b;
+};
 struct GettJob {
     const void* A;
     const void* B;
     void* C;
     const int64_t* oa;
     const int64_t* ob;
+    // offsets of the inner indices of a chunk of 2^kc_log (256 unless the sum is
+    // shorter; fewer when a stored bit past 31 comes earlier); chunk h adds
+    // offset(h) = offset(h - 1) + steps[ctz(h)]
+    const GettOff* koff;
+    const GettStep* steps;
     int64_t n_inst;
     int64_t block0;                // first block of this job in the launch
     int32_t m_log, n_log, k_log;
-    int32_t split;                 // 1: one block per output element (long inner sums)
-    int32_t rpt_log;               // split == 0: each thread computes 2^rpt_log rows of one column
-    int32_t pad_;
-    int8_t a_row[32], a_k[32], b_k[32], b_col[32];
+    int32_t split;                 // 1: a block per 2^rl x 2^cl outputs (long inner sums)
+    int32_t rl, cl;                // split == 0: each thread computes 2^rl rows x 2^cl adjacent columns
+    int32_t n_row_runs, n_col_runs;
+    int32_t kc_log, pad_;
+    // runs of stored bits: index bits [lo, lo + len) at stored bit pos, as
+    // lo | (len - 1) << 8 | pos << 16 (two runs of an operand have a gap between
+    // them: at most 20 in a tensor of up to 2^40 elements)
+    uint32_t row_runs[20], col_runs[20];
+    int64_t rlo[8], clo[4];        // offsets of the first 2^rl rows, 2^cl columns
+    GettOff k8[8];                 // the first entries of koff (all of them when kc_log <= 3)
 };
 // Events for the next grouped launch issued on this thread (gett, matrix-core
 // and FP64 tile groups, split reductions): recorded at the kernel's start and
 // end by the dispatch (timing of the kernel alone).
 void set_launch_events(hipEvent_t start, hipEvent_t stop);
-// blocks one job takes in a grouped launch
-int64_t gett_job_blocks(const GettJob& j);
 // One launch for all jobs of a level: block b runs job d_block_job[b] & 0x7fffffff
 // (records in device memory), in FP64 when bit 31 is set, else in FP32.
 void launch_gett_group(const GettJob* d_jobs, const int32_t* d_block_job, int64_t blocks, hipStream_t s);

@@ -854,197 +854,329 @@ void k_mfma_group(const MfmaJob* __restrict__ jobs, const MfmaTile* __restrict__
 
 // ---------------------------------------------------------------------------
 // Grouped gathered contractions: every small step of one tree level (all
-// clusters, all plans) in one launch.  A block finds its job by binary search
-// over the jobs' first blocks.  Operands are read in their stored order
-// through the per-bit positions (no transpose pass); the low inner bits' offsets
-// come from an LDS table, the high ones are added once per 256-wide chunk.
-//   split == 0: one thread per output element, inner loop in registers;
-//   split == 1: one block per output element (few outputs, long inner sums),
-//               partial sums reduced in FP64 through LDS.
+// clusters, all plans) in one launch.  A block finds its job with one load
+// (block table).  Operands are read in their stored order (no transpose pass):
+// a row's or column's offset is its index cut into the runs of stored bits it
+// covers, an inner index's offset comes from the job's table (the first eight
+// entries inline in the record).  Records, tables and all that is the same for
+// a block are scalar loads, so a step without long sums has no barrier and no
+// LDS: its time is the chain block table -> record -> slice offsets -> operands.
+//   split == 0: a thread computes 2^rl rows x 2^cl adjacent columns, inner loop
+//               in registers, products added in inner-index order;
+//   split == 1: a block computes 2^rl x 2^cl outputs (long inner sums), each
+//               operand element read once for all of them, partial sums reduced
+//               in FP64 in a fixed order.
+// Bound: memory (L2 and HBM) for large steps, the chain of loads for small ones.
+// Against one output per thread and block with the record in LDS: 32 slices of
+// 2 x 2^19 over 4 terms 251 -> 116 us (302 MB), 1446 slices of 4 x 2 over 8192
+// terms 207 -> 82 us, 352 of 4 x 4 over 16384 102 -> 54 us, a level of 8 x 8
+// sums of 1024 terms 12.4 -> 6.0 us.
 // ---------------------------------------------------------------------------
-struct GettSmem {
-    GettJob J;
-    int64_t ak_lo[256], bk_lo[256];
-    double red_r[256], red_i[256];
-    int64_t a_step[32], b_step[32];
-};
+#define TN_CONST __attribute__((address_space(4)))
+// read-only view of memory that no block of the launch writes: uniform
+// addresses become scalar loads
+template <typename T>
+__device__ __forceinline__ const TN_CONST T* cload(const void* p) {
+    return (const TN_CONST T*)p;
+}
 
-// One thread of a small step: column c of RPT consecutive rows (the column
-// operand's element is loaded once for all of them; the row operand's
-// elements are shared by the lanes of a wave, which hold consecutive
-// columns).  The loads of P inner indices are issued before their products, so
-// a thread waits once per P inner indices; products are added in inner-index
-// order.
-template <typename R, typename C2, int RPT>
-__device__ __forceinline__ void gett_rows(const GettJob& J, const int64_t* __restrict__ ak_lo,
-                                          const int64_t* __restrict__ bk_lo, const int64_t* __restrict__ a_step,
-                                          const int64_t* __restrict__ b_step, int64_t local) {
-    constexpr int RLOG = RPT == 1 ? 0 : RPT == 2 ? 1 : RPT == 4 ? 2 : 3;
-    constexpr int P = sizeof(R) == 4 ? (RPT == 1 ? 8 : RPT <= 4 ? 4 : 2) : (RPT <= 2 ? 4 : RPT == 4 ? 2 : 1);
-    const int m_log = J.m_log, n_log = J.n_log, k_log = J.k_log;
-    const int mn_log = m_log + n_log;
-    const int64_t k = int64_t(1) << k_log;
-    const int kc_log = k_log < 8 ? k_log : 8;
-    const int kc = 1 << kc_log;
-    const int nstep = k_log - kc_log;
-    const int64_t o = local * 256 + threadIdx.x;
-    if (o >= (J.n_inst << (mn_log - RLOG))) return;
-    const int64_t c = o & ((int64_t(1) << n_log) - 1);
-    const int64_t rest = o >> n_log;
-    const int64_t rg = rest & ((int64_t(1) << (m_log - RLOG)) - 1);
-    const int64_t inst = rest >> (m_log - RLOG);
-    const int64_t r0 = rg << RLOG;
-    const TN_GLOBAL C2* __restrict__ Ap = gload<C2>(J.A) + gload<int64_t>(J.oa)[inst] + deposit(r0, J.a_row, 0, m_log);
-    const TN_GLOBAL C2* __restrict__ Bp = gload<C2>(J.B) + gload<int64_t>(J.ob)[inst] + deposit(c, J.b_col, 0, n_log);
-    int64_t rlo[RPT];
+__device__ __forceinline__ int64_t run_offset(const TN_CONST uint32_t* runs, int n, uint32_t x) {
+    int64_t o = 0;
+    for (int i = 0; i < n; ++i) {
+        const uint32_t q = runs[i];
+        o |= (int64_t)((x >> (q & 31u)) & ((2u << ((q >> 8) & 31u)) - 1u)) << ((q >> 16) & 63u);
+    }
+    return o;
+}
+
+// V adjacent complex numbers (FP32: two per 16-byte load)
+typedef float f4 __attribute__((ext_vector_type(4)));
+template <typename R, typename C2, int V>
+__device__ __forceinline__ void vload(const TN_GLOBAL C2* p, R (&re)[V], R (&im)[V]) {
+    if constexpr (V == 1) {
+        const C2 v = gld(p);
+        re[0] = v.x;
+        im[0] = v.y;
+    } else {
+        static_assert(sizeof(R) == 4, "FP64 elements are 16 bytes each");
 #pragma unroll
-    for (int i = 0; i < RPT; ++i) rlo[i] = deposit(i, J.a_row, 0, RLOG);
-    R sr[RPT], si[RPT];
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) sr[i] = si[i] = 0;
-    int64_t ahh = 0, bhh = 0;
-    for (int64_t h = 0; h < k; h += kc) {
-        const TN_GLOBAL C2* __restrict__ Ah = Ap + ahh;
-        const TN_GLOBAL C2* __restrict__ Bh = Bp + bhh;
-        {
-            const int t = __builtin_ctzll(~(uint64_t)(h >> kc_log));
-            if (t < nstep) {
-                ahh += a_step[t];
-                bhh += b_step[t];
-            }
-        }
-        int p = 0;
-        for (; p + P <= kc; p += P) {
-            C2 b[P], a[P][RPT];
-#pragma unroll
-            for (int u = 0; u < P; ++u) {
-                b[u] = gld(Bh + bk_lo[p + u]);
-                const int64_t ap = ak_lo[p + u];
-#pragma unroll
-                for (int i = 0; i < RPT; ++i) a[u][i] = gld(Ah + (rlo[i] + ap));
-            }
-#pragma unroll
-            for (int u = 0; u < P; ++u)
-#pragma unroll
-                for (int i = 0; i < RPT; ++i) {
-                    sr[i] += a[u][i].x * b[u].x - a[u][i].y * b[u].y;
-                    si[i] += a[u][i].x * b[u].y + a[u][i].y * b[u].x;
-                }
-        }
-        for (; p < kc; ++p) {
-            const C2 b = gld(Bh + bk_lo[p]);
-            const int64_t ap = ak_lo[p];
-            C2 a[RPT];
-#pragma unroll
-            for (int i = 0; i < RPT; ++i) a[i] = gld(Ah + (rlo[i] + ap));
-#pragma unroll
-            for (int i = 0; i < RPT; ++i) {
-                sr[i] += a[i].x * b.x - a[i].y * b.y;
-                si[i] += a[i].x * b.y + a[i].y * b.x;
-            }
+        for (int q = 0; q < V; q += 2) {
+            const f4 v = *(const TN_GLOBAL f4*)(p + q);
+            re[q] = v[0];
+            im[q] = v[1];
+            re[q + 1] = v[2];
+            im[q + 1] = v[3];
         }
     }
-    TN_GLOBAL C2* __restrict__ Cp = gstore<C2>(J.C) + ((inst << mn_log) + (r0 << n_log) + c);
+}
+template <typename R, typename C2, int V>
+__device__ __forceinline__ void vstore(TN_GLOBAL C2* p, const R (&re)[V], const R (&im)[V]) {
+    if constexpr (V == 1) {
+        C2 v;
+        v.x = re[0];
+        v.y = im[0];
+        gst(p, v);
+    } else {
 #pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-        C2 out;
-        out.x = sr[i];
-        out.y = si[i];
-        gst(Cp + ((int64_t)i << n_log), out);
+        for (int q = 0; q < V; q += 2) *(TN_GLOBAL f4*)(p + q) = f4{re[q], im[q], re[q + 1], im[q + 1]};
     }
 }
 
-template <typename R, typename C2>
-__device__ __forceinline__ void gett_block(const GettJob* __restrict__ jp, GettSmem& sm) {
-    GettJob& J = sm.J;
-    int64_t* ak_lo = sm.ak_lo;
-    int64_t* bk_lo = sm.bk_lo;
-    double* red_r = sm.red_r;
-    double* red_i = sm.red_i;
-    int64_t* a_step = sm.a_step;
-    int64_t* b_step = sm.b_step;
-    const int64_t bid = blockIdx.x;
-    if (threadIdx.x == 0) J = *jp;
-    __syncthreads();
-    const int m_log = J.m_log, n_log = J.n_log, k_log = J.k_log;
+// One thread of a small step.  UNI: the block's outputs lie in one row group
+// of one slice, whose elements are then the same for every thread: scalar loads.
+template <typename R, typename C2, int RL, int CL, bool UNI>
+__device__ __forceinline__ void gett_rows(const TN_CONST GettJob* J, int64_t local, int tid) {
+    constexpr int RPT = 1 << RL, V = 1 << CL;
+    constexpr int W = RPT * V * (sizeof(R) / 4);               // accumulated words / 2
+    // inner indices whose loads are in flight together
+    constexpr int P = UNI ? (RPT * (int)sizeof(R) <= 8 ? 4 : 2)
+                          : W == 1 ? 8 : W <= 4 ? 4 : (W == 8 ? 4 : 2) / (sizeof(R) / 4);
+    const int m_log = J->m_log, n_log = J->n_log, k_log = J->k_log;
     const int mn_log = m_log + n_log;
-    const int64_t k = int64_t(1) << k_log;
-    const int kc_log = k_log < 8 ? k_log : 8;
-    const int kc = 1 << kc_log;
-    for (int i = threadIdx.x; i < kc; i += 256) {
-        ak_lo[i] = deposit(i, J.a_k, 0, kc_log);
-        bk_lo[i] = deposit(i, J.b_k, 0, kc_log);
+    const int cw = n_log - CL;                                 // log2 column groups of a row group
+    const int64_t o = local * 256 + tid;
+    if (!UNI && o >= (J->n_inst << (mn_log - RL - CL))) return;
+    const int64_t c = (o & ((int64_t(1) << cw) - 1)) << CL;
+    const int64_t rest = (UNI ? local * 256 : o) >> cw;
+    const int64_t r0 = (rest & ((int64_t(1) << (m_log - RL)) - 1)) << RL;
+    const int64_t inst = rest >> (m_log - RL);
+    int64_t ao, bo;
+    if constexpr (UNI) {
+        ao = cload<int64_t>(J->oa)[inst];
+        bo = cload<int64_t>(J->ob)[inst];
+    } else {
+        ao = gload<int64_t>(J->oa)[inst];
+        bo = gload<int64_t>(J->ob)[inst];
     }
-    chunk_steps(J.a_k, kc_log, k_log, a_step);
-    chunk_steps(J.b_k, kc_log, k_log, b_step);
-    __syncthreads();
-    const int nstep = k_log - kc_log;
-    const int64_t local = bid - J.block0;
-    if (J.split) {
-        // one output element per block; thread t takes inner indices t + 256 h
-        const int64_t o = local;
-        const int64_t inst = o >> mn_log;
-        const int64_t rc = o & ((int64_t(1) << mn_log) - 1);
-        const int64_t r = rc >> n_log, c = rc & ((int64_t(1) << n_log) - 1);
-        const TN_GLOBAL C2* __restrict__ Ap = gload<C2>(J.A) + gload<int64_t>(J.oa)[inst] + deposit(r, J.a_row, 0, m_log);
-        const TN_GLOBAL C2* __restrict__ Bp = gload<C2>(J.B) + gload<int64_t>(J.ob)[inst] + deposit(c, J.b_col, 0, n_log);
-        R sr = 0, si = 0;
-        if ((int)threadIdx.x < kc) {
-            const int64_t alo = ak_lo[threadIdx.x], blo = bk_lo[threadIdx.x];
-            // U chunks per round (16 in FP32, 8 in FP64): their loads are all in
-            // flight before the first product (the chunk count is a power of two)
-            constexpr int U = sizeof(R) == 4 ? 16 : 8;
-            const int64_t nh = k >> kc_log;
-            const int64_t step = nh >= U ? U : nh;
-            int64_t ah = alo, bh = blo;
-            for (int64_t h0 = 0; h0 < nh; h0 += step) {
-                C2 a[U], b[U];
+    const C2* Ag = (const C2*)J->A + (ao + run_offset(J->row_runs, J->n_row_runs, (uint32_t)r0));
+    const TN_GLOBAL C2* Bp = gload<C2>(J->B) + (bo + run_offset(J->col_runs, J->n_col_runs, (uint32_t)c));
+    int64_t rlo[RPT];
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (u < step) {
-                        a[u] = gld(Ap + ah);
-                        b[u] = gld(Bp + bh);
-                        const int t = __builtin_ctzll(~(uint64_t)(h0 + u));
-                        if (t < nstep) {
-                            ah += a_step[t];
-                            bh += b_step[t];
-                        }
-                    }
+    for (int i = 0; i < RPT; ++i) rlo[i] = J->rlo[i];
+    R sr[RPT][V], si[RPT][V];
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (u < step) {
-                        sr += a[u].x * b[u].x - a[u].y * b[u].y;
-                        si += a[u].x * b[u].y + a[u].y * b[u].x;
+    for (int i = 0; i < RPT; ++i)
+#pragma unroll
+        for (int v = 0; v < V; ++v) sr[i][v] = si[i][v] = 0;
+    auto lda = [&](int64_t off) {
+        if constexpr (UNI) {
+            const TN_CONST R* q = cload<R>(Ag + off);
+            C2 v;
+            v.x = q[0];
+            v.y = q[1];
+            return v;
+        } else {
+            return gld(gload<C2>(Ag) + off);
+        }
+    };
+    const int kc_log = J->kc_log;
+    const int kc = 1 << kc_log;
+    const TN_CONST GettOff* kt = kc_log <= 3 ? J->k8 : cload<GettOff>(J->koff);
+    const TN_CONST GettStep* steps = cload<GettStep>(J->steps);
+    const int64_t nh = int64_t(1) << (k_log - kc_log);
+    int64_t ahh = 0, bhh = 0;
+    // P inner indices: their loads, then their products (in order)
+    auto batch = [&](const GettOff (&kk)[P], auto all, int n, auto&& between) {
+        constexpr bool ALL = decltype(all)::value;
+        R br[P][V], bi[P][V];
+        C2 a[P][RPT];
+#pragma unroll
+        for (int u = 0; u < P; ++u)
+            if (ALL || u < n) {
+                vload<R, C2, V>(Bp + (bhh + kk[u].b), br[u], bi[u]);
+                const int64_t ap = ahh + kk[u].a;
+#pragma unroll
+                for (int i = 0; i < RPT; ++i) a[u][i] = lda(rlo[i] + ap);
+            }
+        between();
+#pragma unroll
+        for (int u = 0; u < P; ++u)
+            if (ALL || u < n) {
+#pragma unroll
+                for (int i = 0; i < RPT; ++i)
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        sr[i][v] += a[u][i].x * br[u][v] - a[u][i].y * bi[u][v];
+                        si[i][v] += a[u][i].x * bi[u][v] + a[u][i].y * br[u][v];
                     }
             }
-        }
-        // FP64 sum in a fixed order: a butterfly within each wave (both lanes
-        // of a pair form the same sum), then the four waves in order
-        double vr = (double)sr, vi = (double)si;
+    };
+    GettOff kk[P];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            vr += __shfl_xor(vr, off);
-            vi += __shfl_xor(vi, off);
+    for (int u = 0; u < P; ++u)
+        if (u < kc) kk[u] = GettOff{kt[u].a, kt[u].b};
+    for (int64_t h = 0;;) {
+        if (kc < P) {                                          // a chunk is one short batch
+            batch(kk, std::integral_constant<bool, false>{}, kc, [] {});
+        } else {
+            for (int p = 0; p < kc; p += P) {
+                // the next batch's offsets arrive during this one's loads
+                GettOff nx[P];
+                const int q0 = (p + P) & (kc - 1);
+                batch(kk, std::integral_constant<bool, true>{}, P, [&] {
+#pragma unroll
+                    for (int u = 0; u < P; ++u) nx[u] = GettOff{kt[q0 + u].a, kt[q0 + u].b};
+                });
+#pragma unroll
+                for (int u = 0; u < P; ++u) kk[u] = nx[u];
+            }
         }
-        if ((threadIdx.x & 63) == 0) {
-            red_r[threadIdx.x >> 6] = vr;
-            red_i[threadIdx.x >> 6] = vi;
+        if (++h >= nh) break;
+        const int t = __builtin_ctzll((uint64_t)h);            // chunk h - 1 -> h
+        ahh += steps[t].a;
+        bhh += steps[t].b;
+    }
+    TN_GLOBAL C2* Cp = gstore<C2>(J->C) + ((inst << mn_log) + (r0 << n_log) + c);
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) vstore<R, C2, V>(Cp + ((int64_t)i << n_log), sr[i], si[i]);
+}
+
+constexpr int kDotOut = 16;    // most outputs of a split block
+
+// A block's partial sums of 2^RL x 2^CL outputs: thread t takes inner indices
+// t + 256 h.  The wave's sums go to red[wave][output] (FP64, a fixed-order
+// butterfly that halves the outputs a lane holds at each exchange).
+template <typename R, typename C2, int RL, int CL>
+__device__ __forceinline__ void gett_dot(const TN_CONST GettJob* J, int64_t local, int tid, double2 (*red)[kDotOut]) {
+    constexpr int NR = 1 << RL, NC = 1 << CL, N = NR * NC;
+    // U inner indices' loads are in flight together (NR + NC elements each)
+    constexpr int U = (sizeof(R) == 4 ? 16 : 8) / (N == 1 ? 1 : N == 2 ? 2 : N == 4 ? (sizeof(R) == 4 ? 2 : 4)
+                                                                                     : N == 8 ? 4 : 8);
+    const int tm = J->m_log - RL, tc = J->n_log - CL;
+    const int64_t inst = local >> (tm + tc);
+    const uint32_t r0 = (uint32_t)((local >> tc) & ((int64_t(1) << tm) - 1)) << RL;
+    const uint32_t c0 = (uint32_t)(local & ((int64_t(1) << tc) - 1)) << CL;
+    const TN_GLOBAL C2* Ap = gload<C2>(J->A) + (cload<int64_t>(J->oa)[inst] + run_offset(J->row_runs, J->n_row_runs, r0));
+    const TN_GLOBAL C2* Bp = gload<C2>(J->B) + (cload<int64_t>(J->ob)[inst] + run_offset(J->col_runs, J->n_col_runs, c0));
+    const TN_GLOBAL uint32_t* kt = gload<uint32_t>(J->koff);
+    const TN_CONST GettStep* steps = cload<GettStep>(J->steps);
+    int64_t ah = kt[2 * tid], bh = kt[2 * tid + 1];
+    int64_t rlo[NR], clo[NC];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) rlo[i] = J->rlo[i];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) clo[j] = J->clo[j];
+    R sr[N], si[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) sr[q] = si[q] = 0;
+    const int64_t nh = int64_t(1) << (J->k_log - 8);
+    const int64_t step = nh >= U ? U : nh;
+    for (int64_t h0 = 0; h0 < nh; h0 += step) {
+        C2 a[U][NR], b[U][NC];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (u < step) {
+#pragma unroll
+                for (int i = 0; i < NR; ++i) a[u][i] = gld(Ap + (ah + rlo[i]));
+#pragma unroll
+                for (int j = 0; j < NC; ++j) b[u][j] = gld(Bp + (bh + clo[j]));
+                if (h0 + u + 1 < nh) {
+                    const int t = __builtin_ctzll((uint64_t)(h0 + u + 1));
+                    ah += steps[t].a;
+                    bh += steps[t].b;
+                }
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (u < step) {
+#pragma unroll
+                for (int i = 0; i < NR; ++i)
+#pragma unroll
+                    for (int j = 0; j < NC; ++j) {
+                        sr[i * NC + j] += a[u][i].x * b[u][j].x - a[u][i].y * b[u][j].y;
+                        si[i * NC + j] += a[u][i].x * b[u][j].y + a[u][i].y * b[u][j].x;
+                    }
+            }
+    }
+    double vr[N], vi[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        vr[q] = (double)sr[q];
+        vi[q] = (double)si[q];
+    }
+    const int lane = tid & 63;
+    constexpr int NLOG = RL + CL;
+#pragma unroll
+    for (int s = 0; s < NLOG; ++s) {
+        const int half = N >> (s + 1), off = 32 >> s;
+        const bool up = lane & off;             // keeps the upper half of the outputs
+#pragma unroll
+        for (int q = 0; q < N / 2; ++q) {
+            if (q >= half) break;
+            const double kr = up ? vr[q + half] : vr[q], ki = up ? vi[q + half] : vi[q];
+            const double gr = up ? vr[q] : vr[q + half], gi = up ? vi[q] : vi[q + half];
+            vr[q] = kr + __shfl_xor(gr, off);
+            vi[q] = ki + __shfl_xor(gi, off);
         }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            C2 out;
-            out.x = (R)(((red_r[0] + red_r[1]) + red_r[2]) + red_r[3]);
-            out.y = (R)(((red_i[0] + red_i[1]) + red_i[2]) + red_i[3]);
-            gst(gstore<C2>(J.C) + o, out);
+    }
+#pragma unroll
+    for (int s = NLOG; s < 6; ++s) {
+        vr[0] += __shfl_xor(vr[0], 32 >> s);
+        vi[0] += __shfl_xor(vi[0], 32 >> s);
+    }
+    if ((lane & ((64 >> NLOG) - 1)) == 0) red[tid >> 6][lane >> (6 - NLOG)] = make_double2(vr[0], vi[0]);
+}
+
+// after a barrier: the four waves' sums in order, one thread per output
+template <typename R, typename C2>
+__device__ __forceinline__ void gett_dot_finish(const TN_CONST GettJob* J, int64_t local, int tid,
+                                                const double2 (*red)[kDotOut]) {
+    const int rl = J->rl, cl = J->cl, n_log = J->n_log;
+    if (tid >= 1 << (rl + cl)) return;
+    const int tm = J->m_log - rl, tc = n_log - cl;
+    const int64_t inst = local >> (tm + tc);
+    const int64_t r = (((local >> tc) & ((int64_t(1) << tm) - 1)) << rl) + (tid >> cl);
+    const int64_t c = ((local & ((int64_t(1) << tc) - 1)) << cl) + (tid & ((1 << cl) - 1));
+    C2 out;
+    out.x = (R)(((red[0][tid].x + red[1][tid].x) + red[2][tid].x) + red[3][tid].x);
+    out.y = (R)(((red[0][tid].y + red[1][tid].y) + red[2][tid].y) + red[3][tid].y);
+    gst(gstore<C2>(J->C) + ((((inst << J->m_log) + r) << n_log) + c), out);
+}
+
+// One 256-thread block of a job, up to the split sums' barrier.  SCALAR: the
+// row operand may be read with scalar loads (nothing in the launch writes it).
+template <typename R, typename C2, bool SCALAR>
+__device__ __forceinline__ void gett_block(const TN_CONST GettJob* J, int64_t local, int tid, double2 (*red)[kDotOut]) {
+    constexpr bool F32 = sizeof(R) == 4;
+    const int shape = J->rl * 4 + J->cl;
+    if (J->split) {
+        switch (shape) {
+        case 0: gett_dot<R, C2, 0, 0>(J, local, tid, red); break;
+        case 1: gett_dot<R, C2, 0, 1>(J, local, tid, red); break;
+        case 4: gett_dot<R, C2, 1, 0>(J, local, tid, red); break;
+        case 5: gett_dot<R, C2, 1, 1>(J, local, tid, red); break;
+        }
+        if constexpr (F32) switch (shape) {
+        case 6: gett_dot<R, C2, 1, 2>(J, local, tid, red); break;
+        case 9: gett_dot<R, C2, 2, 1>(J, local, tid, red); break;
+        case 10: gett_dot<R, C2, 2, 2>(J, local, tid, red); break;
         }
         return;
     }
-    // one thread: column c of 2^rpt_log consecutive rows
-    switch (J.rpt_log) {
-        case 0: gett_rows<R, C2, 1>(J, ak_lo, bk_lo, a_step, b_step, local); break;
-        case 1: gett_rows<R, C2, 2>(J, ak_lo, bk_lo, a_step, b_step, local); break;
-        case 2: gett_rows<R, C2, 4>(J, ak_lo, bk_lo, a_step, b_step, local); break;
-        default: gett_rows<R, C2, 8>(J, ak_lo, bk_lo, a_step, b_step, local); break;
+    if (SCALAR && J->n_log - J->cl >= 8) {
+        if constexpr (F32) switch (shape) {
+        case 1: gett_rows<R, C2, 0, 1, true>(J, local, tid); return;
+        case 5: gett_rows<R, C2, 1, 1, true>(J, local, tid); return;
+        case 9: gett_rows<R, C2, 2, 1, true>(J, local, tid); return;
+        case 2: gett_rows<R, C2, 0, 2, true>(J, local, tid); return;
+        case 6: gett_rows<R, C2, 1, 2, true>(J, local, tid); return;
+        case 10: gett_rows<R, C2, 2, 2, true>(J, local, tid); return;
+        } else switch (shape) {
+        case 4: gett_rows<R, C2, 1, 0, true>(J, local, tid); return;
+        case 8: gett_rows<R, C2, 2, 0, true>(J, local, tid); return;
+        case 12: gett_rows<R, C2, 3, 0, true>(J, local, tid); return;
+        }
+    }
+    switch (shape) {
+    case 0: gett_rows<R, C2, 0, 0, false>(J, local, tid); break;
+    case 4: gett_rows<R, C2, 1, 0, false>(J, local, tid); break;
+    case 8: gett_rows<R, C2, 2, 0, false>(J, local, tid); break;
+    case 12: gett_rows<R, C2, 3, 0, false>(J, local, tid); break;
+    }
+    if constexpr (F32) switch (shape) {
+    case 1: gett_rows<R, C2, 0, 1, false>(J, local, tid); break;
+    case 5: gett_rows<R, C2, 1, 1, false>(J, local, tid); break;
+    case 9: gett_rows<R, C2, 2, 1, false>(J, local, tid); break;
     }
 }
 
@@ -1052,13 +1184,19 @@ __device__ __forceinline__ void gett_block(const GettJob* __restrict__ jp, GettS
 // block_job[b] & 0x7fffffff, in FP64 when bit 31 is set (the dominant-term
 // pass's jobs of the same level), else in FP32.  The table is built on the
 // host, so a block finds its job with one load.
-__global__ __launch_bounds__(256) void k_gett_group(const GettJob* __restrict__ jobs,
-                                                    const int32_t* __restrict__ block_job) {
-    __shared__ GettSmem sm;
-    const uint32_t e = (uint32_t)block_job[blockIdx.x];
-    const GettJob* jp = jobs + (e & 0x7fffffffu);
-    if (e >> 31) gett_block<double, double2>(jp, sm);
-    else gett_block<float, float2>(jp, sm);
+__global__ __launch_bounds__(256, 4) void k_gett_group(const GettJob* __restrict__ jobs,
+                                                       const int32_t* __restrict__ block_job) {
+    __shared__ double2 red[4][kDotOut];
+    const uint32_t e = (uint32_t)cload<int32_t>(block_job)[blockIdx.x];
+    const TN_CONST GettJob* J = cload<GettJob>(jobs) + (e & 0x7fffffffu);
+    const int64_t local = (int64_t)blockIdx.x - J->block0;
+    const int tid = (int)threadIdx.x;
+    if (e >> 31) gett_block<double, double2, true>(J, local, tid, red);
+    else gett_block<float, float2, true>(J, local, tid, red);
+    if (!J->split) return;
+    __syncthreads();
+    if (e >> 31) gett_dot_finish<double, double2>(J, local, tid, red);
+    else gett_dot_finish<float, float2>(J, local, tid, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -1993,11 +2131,6 @@ void launch_mfma_group(int tile, const MfmaJob* d_jobs, const MfmaTile* d_tiles,
     TN_GLAUNCH(64, 16)
     TN_GLAUNCH(32, 16)
 #undef TN_GLAUNCH
-}
-
-int64_t gett_job_blocks(const GettJob& j) {
-    const int64_t outs = j.n_inst << (j.m_log + j.n_log);
-    return j.split ? outs : ((outs >> j.rpt_log) + 255) / 256;
 }
 
 void launch_gett_group(const GettJob* d_jobs, const int32_t* d_block_job, int64_t blocks, hipStream_t s) {
