@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -171,6 +172,8 @@ struct Launch {
     Ref jobs;
     int n_jobs = 0;
     int64_t blocks = 0;
+    int chain = -1;                               // runs inside this chain launch (tn_exec_s::chains)
+    bool chain_head = false;                      // the chain is issued in this launch's place
     std::vector<struct GroupJob> hjobs;
     // grouped matrix-core launch (L_MGROUP); L_MREDUCE shares its job and tile
     // records (written by the L_MGROUP launch it follows)
@@ -178,6 +181,18 @@ struct Launch {
     Ref tiles;
     int64_t n_tiles = 0;
     std::vector<struct MJob> mjobs;
+};
+
+// Consecutive grouped launches that run as one (k_gett_chain).
+struct Chain {
+    Ref parts, blocks;                 // GettChainPart / GettChainBlock arrays (constants)
+    int n_parts = 0;
+    struct Block {
+        const Launch* launch;          // filled when the launch lists are final
+        int launch_index, job;
+        int64_t local;
+    };
+    std::vector<Block> hblocks;
 };
 
 struct PlanExec {
@@ -229,11 +244,13 @@ struct tn_exec_s {
     std::vector<tn::Launch> plain_launches; // PLAIN mode per-term body
     std::vector<tn::Launch> launches_const; // slot-free steps: run once per binding (and upload)
     std::vector<tn::Launch> tail;           // finalize + level sums
+    std::vector<tn::Chain> chains;
+    bool probe = false;                     // built for its shapes only (see build_exec)
     // packed circuits: the tail runs as one finalize and one level-sum launch
     // the tail of all packed circuits: one record per circuit, the per-block
     // level partials of the term launch
     tn::Ref tail_jobs, tail_part;
-    int64_t tail_blocks = 0;
+    int64_t tail_blocks = 0, tail_most = 0;   // of all circuits; of the largest
     int tail_levels = 0;
     std::vector<tn::PlanExec> plans;
     // results of an estimate (level sums, FP32 all-dominant value of every
@@ -380,13 +397,26 @@ struct GroupJob {
     int m_log = 0, n_log = 0, k_log = 0, split = 0;
     int rl = 0, cl = 0;        // log2 rows and columns of a thread (split: of a block)
     Ref koff, steps;           // offsets inside a chunk (chunks of over 8; shorter ones are in the record)
+    int64_t a_len = 0, b_len = 0, c_len = 0;   // bytes of the operands (all instances) and of the result
     int8_t a_row[32] = {}, a_k[32] = {}, b_k[32] = {}, b_col[32] = {};
     double flops = 0, bytes = 0;
 };
 
+// log2 of a small step's chunk of inner indices: 256, or fewer where an offset
+// inside the chunk would pass 32 bits
+static int kc_log_of(const GroupJob& j) {
+    int q = 0;
+    while (q < j.k_log && q < 8 && j.a_k[q] < 32 && j.b_k[q] < 32) ++q;
+    return q;
+}
+
+// Most outputs of a small step whose sums run on four waves each (512 blocks of
+// 64 outputs, two per CU: more outputs keep the CUs busy with a thread each).
+constexpr int64_t kQuarterMaxOuts = int64_t(1) << 15;
+
 static int64_t job_blocks(const GroupJob& j) {
     const int64_t units = j.n_inst << (j.m_log + j.n_log - j.rl - j.cl);
-    return j.split ? units : (units + 255) / 256;
+    return j.split == 1 ? units : j.split == 2 ? (units + 63) / 64 : (units + 255) / 256;
 }
 
 // Outputs per thread (per block with split sums) of a small step.
@@ -406,6 +436,13 @@ static void gett_shape(GroupJob& j) {
             j.cl = q[1];
             return;
         }
+        return;
+    }
+    // few outputs and a sum that one thread would walk in two batches of loads
+    // or more: four waves per output (1024 FP64 outputs of 128 terms each, 4
+    // blocks: 18.5 us a launch with a thread per output, 7.8 us)
+    if (outs <= kQuarterMaxOuts && j.k_log >= (j.fp64 ? 4 : 5) && kc_log_of(j) == std::min(j.k_log, 8)) {
+        j.split = 2;
         return;
     }
     // at least 64K threads stay busy; FP32 columns that are adjacent in the
@@ -429,19 +466,12 @@ static int64_t place_bits(int64_t x, const int8_t* pos, int n) {
     return o;
 }
 
-// log2 of a small step's chunk of inner indices: 256, or fewer where an offset
-// inside the chunk would pass 32 bits
-static int kc_log_of(const GroupJob& j) {
-    int q = 0;
-    while (q < j.k_log && q < 8 && j.a_k[q] < 32 && j.b_k[q] < 32) ++q;
-    return q;
-}
-
 static std::vector<GettOff> gett_offsets(const GroupJob& j) {
     const int kc_log = kc_log_of(j);
-    std::vector<GettOff> t;
-    for (int64_t p = 0; p < (int64_t(1) << kc_log); ++p)
-        t.push_back({(uint32_t)place_bits(p, j.a_k, kc_log), (uint32_t)place_bits(p, j.b_k, kc_log)});
+    std::vector<GettOff> t(size_t(1) << kc_log, GettOff{0, 0});
+    for (int q = 0; q < kc_log; ++q)
+        for (size_t p = 0; p < size_t(1) << q; ++p)
+            t[p + (size_t(1) << q)] = {t[p].a + (1u << j.a_k[q]), t[p].b + (1u << j.b_k[q])};
     return t;
 }
 
@@ -1201,6 +1231,9 @@ struct Builder {
                 jb.n_log = (int)FQ.size();
                 jb.k_log = rk;
                 jb.n_inst = ninst * nbatch;
+                jb.a_len = bytesR * esz;
+                jb.b_len = bytesQ * esz;
+                jb.c_len = C.bytes;
                 jb.split = split_sum ? 1 : 0;
                 for (size_t q = 0; q < row_bits.size(); ++q) jb.a_row[q] = (int8_t)posin(R, row_bits[q]);
                 for (size_t q = 0; q < k_bits.size(); ++q) {
@@ -1575,6 +1608,118 @@ static void merge_fp64_chain(tn_exec_s* ex) {
     ex->launches64.clear();
 }
 
+// Runs of consecutive grouped launches whose levels are small enough for one
+// block per independent part (k_gett_chain).  A launch joins while every part's
+// blocks of its level, four at a time, take no longer than a launch of its own:
+// about 1.2 us per round plus 0.6 us per batch of loads of its longest sum,
+// against 3.5 us more for a launch than for a round (8-qubit chain, 3 levels of
+// 1 to 6 blocks and the tail: 37.4 us an estimate as 5 launches, 29.6 as 2).
+static void plan_chains(tn_exec_s* ex, std::vector<Launch>& list) {
+    constexpr size_t kMaxJobs = 400;
+    constexpr int kMaxBlocks = 12;                     // of a part at one level
+    struct Span {
+        int64_t a0, a1, b0, b1, c0, c1;                // bytes read (a, b) and written (c), regions apart
+    };
+    auto at = [](const Ref& r) { return r.off + ((int64_t)r.region << 57); };
+    std::vector<const GroupJob*> jobs;
+    std::vector<Span> span;
+    std::vector<int> parent, launch_of, job_of, was;
+    std::vector<std::array<int16_t, kChainLevels>> cnt, cnt_was;   // of a part's root: blocks per level
+    auto find = [&](int x) {
+        while (parent[x] != x) x = parent[x] = parent[parent[x]];
+        return x;
+    };
+    for (size_t i = 0; i < list.size();) {
+        jobs.clear();
+        span.clear();
+        parent.clear();
+        launch_of.clear();
+        job_of.clear();
+        cnt.clear();
+        size_t j = i;
+        for (; j < list.size() && list[j].kind == L_GROUP && j - i < (size_t)kChainLevels; ++j) {
+            const Launch& L = list[j];
+            if (jobs.size() + L.hjobs.size() > kMaxJobs) break;
+            const int lv = (int)(j - i);
+            double batches = 1;
+            for (const GroupJob& g : L.hjobs) {
+                const double k = std::ldexp(1.0, g.k_log) / (g.split == 1 ? 256 : g.split == 2 ? 4 : 1);
+                batches = std::max(batches, k / (g.split == 1 ? (g.fp64 ? 8 : 16) : (g.fp64 ? 4 : 8)));
+            }
+            const double t = 1.2 + 0.6 * batches;
+            const int64_t most = std::min<int64_t>(kMaxBlocks, 4 * (int64_t)(1.0 + 3.5 / t));
+            bool ok = true;
+            for (const GroupJob& g : L.hjobs) ok = ok && g.rl == 0 && g.cl == 0 && job_blocks(g) <= most;
+            if (!ok) break;
+            const size_t n0 = jobs.size();
+            was = parent;
+            cnt_was = cnt;
+            for (size_t q = 0; q < L.hjobs.size(); ++q) {
+                const GroupJob& g = L.hjobs[q];
+                jobs.push_back(&g);
+                span.push_back({at(g.a), at(g.a) + g.a_len, at(g.b), at(g.b) + g.b_len, at(g.c), at(g.c) + g.c_len});
+                parent.push_back((int)parent.size());
+                launch_of.push_back((int)j);
+                job_of.push_back((int)q);
+                cnt.push_back({});
+                cnt.back()[lv] = (int16_t)job_blocks(g);
+            }
+            for (size_t x = n0; x < jobs.size() && ok; ++x)
+                for (size_t y = 0; y < n0; ++y) {
+                    const Span &p = span[x], &q = span[y];
+                    if (!((p.c0 < q.c1 && q.c0 < p.c1) || (p.c0 < q.a1 && q.a0 < p.c1) || (p.c0 < q.b1 && q.b0 < p.c1) ||
+                          (q.c0 < p.a1 && p.a0 < q.c1) || (q.c0 < p.b1 && p.b0 < q.c1)))
+                        continue;
+                    const int u = find((int)x), v = find((int)y);
+                    if (u == v) continue;
+                    parent[u] = v;
+                    for (int l = 0; l <= lv; ++l) {
+                        cnt[v][l] = (int16_t)(cnt[v][l] + cnt[u][l]);
+                        ok = ok && cnt[v][l] <= (l == lv ? most : kMaxBlocks);
+                    }
+                }
+            if (!ok) {
+                jobs.resize(n0);
+                span.resize(n0);
+                launch_of.resize(n0);
+                job_of.resize(n0);
+                parent = was;
+                cnt = cnt_was;
+                break;
+            }
+        }
+        if (j < i + 2) {
+            i = std::max(j, i + 1);
+            continue;
+        }
+        Chain ch;
+        std::map<int, std::vector<int>> part;          // root -> jobs, in level order
+        for (size_t a = 0; a < jobs.size(); ++a) part[find((int)a)].push_back((int)a);
+        std::vector<GettChainPart> parts;
+        for (auto& kv : part) {
+            GettChainPart p{};
+            int lv = -1;
+            for (int a : kv.second) {
+                if (launch_of[a] != lv) p.start[p.n_levels++] = (int)ch.hblocks.size();
+                lv = launch_of[a];
+                if (jobs[a]->split) p.split_levels |= 1u << (p.n_levels - 1);
+                const int64_t nb = job_blocks(*jobs[a]);
+                for (int64_t b = 0; b < nb; ++b) ch.hblocks.push_back({nullptr, launch_of[a], job_of[a], b});
+            }
+            p.start[p.n_levels] = (int)ch.hblocks.size();
+            parts.push_back(p);
+        }
+        ch.n_parts = (int)parts.size();
+        ch.parts = Ref{R_CONST, ex->cbuf.add(parts.data(), (int64_t)(parts.size() * sizeof(GettChainPart)))};
+        ch.blocks = Ref{R_CONST, ex->cbuf.reserve((int64_t)(ch.hblocks.size() * sizeof(GettChainBlock)))};
+        for (auto& b : ch.hblocks) b.launch = &list[b.launch_index];
+        for (size_t q = i; q < j; ++q) list[q].chain = (int)ex->chains.size();
+        list[i].chain_head = true;
+        ex->chains.push_back(std::move(ch));
+        i = j;
+    }
+}
+
 // Fixes the constant region's layout and gives every reference to one of the
 // buffers behind its data its offset.
 static void place_outputs(tn_exec_s* ex) {
@@ -1774,8 +1919,11 @@ static void build_schedule(tn_exec_s* ex, int n, const tn_plan* plans, const tn_
                 L.jobs = Ref{R_CONST, ex->cbuf.reserve((int64_t)L.n_jobs * (int64_t)sizeof(GettJob))};
                 L.table = Ref{R_CONST, ex->cbuf.reserve(L.blocks * 4)};
             }
+    if (!ex->opts.time_kernels && !ex->probe)      // timed launches run one by one
+        for (auto* list : {&ex->launches_const, &ex->launches, &ex->launches64}) plan_chains(ex, *list);
     for (const PlanExec& pe : ex->plans) {
         ex->tail_blocks += (pe.n_terms + 255) / 256;
+        ex->tail_most = std::max(ex->tail_most, (pe.n_terms + 255) / 256);
         ex->tail_levels = std::max(ex->tail_levels, pe.terms->level + 1);
     }
     ex->tail_jobs = Ref{R_CONST, ex->cbuf.reserve((int64_t)n * (int64_t)sizeof(TailJob))};
@@ -1836,8 +1984,8 @@ static void bind(tn_exec_s* ex) {
                 for (int q = 0; q < 1 << h.rl; ++q) j.rlo[q] = place_bits(q, h.a_row, h.rl);
                 for (int q = 0; q < 1 << h.cl; ++q) j.clo[q] = place_bits(q, h.b_col, h.cl);
                 j.kc_log = kc_log_of(h);
-                const std::vector<GettOff> off = gett_offsets(h);
-                for (size_t q = 0; q < off.size() && q < 8; ++q) j.k8[q] = off[q];
+                for (int q = 0; q < 1 << std::min(j.kc_log, 3); ++q)
+                    j.k8[q] = {(uint32_t)place_bits(q, h.a_k, 3), (uint32_t)place_bits(q, h.b_k, 3)};
                 if (j.kc_log > 3) j.koff = (const GettOff*)resolve(ex, h.koff);
                 if (j.kc_log < h.k_log) j.steps = (const GettStep*)resolve(ex, h.steps);
                 const int64_t nb = job_blocks(h);
@@ -1881,6 +2029,13 @@ static void bind(tn_exec_s* ex) {
     for (auto& L : ex->launches) fix(L);
     for (auto& L : ex->launches64) fix(L);
     for (auto& L : ex->plain_launches) fix(L);
+    for (const Chain& ch : ex->chains) {
+        GettChainBlock* d = (GettChainBlock*)(ex->cbuf.bytes.data() + ch.blocks.off);
+        for (size_t q = 0; q < ch.hblocks.size(); ++q) {
+            const Chain::Block& b = ch.hblocks[q];
+            d[q] = {(const GettJob*)resolve(ex, b.launch->jobs) + b.job, b.local, b.launch->hjobs[b.job].fp64, 0};
+        }
+    }
     // pointer tables written into the host staging copy before upload
     for (auto& L : ex->plain_launches)
         if (L.kind == L_SLOTFILL) {
@@ -1939,6 +2094,13 @@ static void enqueue(tn_exec_s* ex, Launch& L, hipStream_t s) {
         else launch_permute_c64(L.p, s);
         break;
     case L_GROUP:
+        if (L.chain >= 0) {
+            if (!L.chain_head) break;
+            const Chain& ch = ex->chains[L.chain];
+            launch_gett_chain((const GettChainPart*)resolve(ex, ch.parts), ch.n_parts,
+                              (const GettChainBlock*)resolve(ex, ch.blocks), s);
+            break;
+        }
         launch_gett_group((const GettJob*)resolve(ex, L.jobs), (const int32_t*)resolve(ex, L.table), L.blocks, s);
         break;
     case L_MGROUP:
@@ -2130,7 +2292,7 @@ static void run_tail(tn_exec_s* ex, hipStream_t s) {
         }
     }
     launch_tail((const TailJob*)resolve(ex, ex->tail_jobs), (int)ex->plans.size(), ex->tail_blocks,
-                ex->tail_levels, (double*)resolve(ex, ex->tail_part), ex->res_shift, s);
+                ex->tail_most, ex->tail_levels, (double*)resolve(ex, ex->tail_part), ex->res_shift, s);
     HIPCHK(hipGetLastError());
 }
 
@@ -2224,6 +2386,7 @@ static std::string describe_exec(const tn_exec_s* ex) {
     auto emit = [&](const Launch& L, const char* phase) {
         os << (first ? "" : ",") << "{\"phase\":\"" << phase << "\",\"kind\":" << L.kind << ",\"fp64\":" << L.fp64
            << ",\"plan\":" << L.plan << ",\"level\":" << L.level << ",\"t_ms\":" << L.t_ms << ",\"t_n\":" << L.t_n;
+        if (L.kind == L_GROUP) os << ",\"chain\":" << L.chain;
         first = false;
         if (L.kind == L_GEMM)
             os << ",\"m_log\":" << L.g.m_log << ",\"n_log\":" << L.g.n_log << ",\"k_log\":" << L.g.k_log
@@ -2302,6 +2465,7 @@ static std::string describe_exec(const tn_exec_s* ex) {
                 arr("a_k", h.a_k, h.k_log);
                 arr("b_k", h.b_k, h.k_log);
                 arr("b_col", h.b_col, h.n_log);
+                os << ",\"len\":[" << h.a_len << "," << h.b_len << "," << h.c_len << "],\"blocks\":" << job_blocks(h);
                 os << ",\"flops\":" << h.flops << ",\"bytes\":" << h.bytes << "}";
             }
             os << "]";
@@ -2329,6 +2493,33 @@ static std::string describe_exec(const tn_exec_s* ex) {
     for (auto& L : ex->launches) emit(L, "batch");
     for (auto& L : ex->plain_launches) emit(L, "plain");
     for (auto& L : ex->tail) emit(L, "tail");
+    // chain launches: per part, its blocks as [launch of the list above, job, block of the job] by level
+    os << "],\"chains\":[";
+    auto index_of = [&](const Launch* L) {
+        int64_t base = 0;
+        for (auto* list : {&ex->launches_const, &ex->launches64, &ex->launches}) {
+            if (L >= list->data() && L < list->data() + list->size()) return base + (int64_t)(L - list->data());
+            base += (int64_t)list->size();
+        }
+        return (int64_t)-1;
+    };
+    for (size_t i = 0; i < ex->chains.size(); ++i) {
+        const Chain& ch = ex->chains[i];
+        os << (i ? ",[" : "[");
+        const GettChainPart* pt = (const GettChainPart*)(ex->cbuf.bytes.data() + ch.parts.off);
+        for (int p = 0; p < ch.n_parts; ++p) {
+            os << (p ? ",[" : "[");
+            for (int l = 0; l < pt[p].n_levels; ++l) {
+                os << (l ? ",[" : "[");
+                for (int b = pt[p].start[l]; b < pt[p].start[l + 1]; ++b)
+                    os << (b > pt[p].start[l] ? ",[" : "[") << index_of(ch.hblocks[b].launch) << "," << ch.hblocks[b].job
+                       << "," << ch.hblocks[b].local << "]";
+                os << "]";
+            }
+            os << "]";
+        }
+        os << "]";
+    }
     os << "],\"plans\":[";
     for (size_t i = 0; i < ex->plans.size(); ++i) {
         const PlanExec& pe = ex->plans[i];
@@ -2392,8 +2583,6 @@ static void issue_estimate(tn_exec_s* ex, hipStream_t s) {
     }
 }
 
-// One circuit's result from its level sums ((sum, comp) pairs, u = 0..level):
-// A(u) as the compensated running sum, and the truncation bound of the split.
 static void fill_one(const Plan& P, const Terms& T, int64_t n_live, int64_t n_zero, const double* sums,
                      double x0_fp32, tn_result& r) {
     std::memset(&r, 0, sizeof(r));
@@ -2478,6 +2667,7 @@ static std::unique_ptr<tn_exec_s> build_exec(int n, const tn_plan* plans, const 
         //    job's shape (measured slower with the merge).
         tn_exec_s probe;
         probe.opts = ex->opts;
+        probe.probe = true;
         build_schedule(&probe, n, plans, terms, nullptr, range);
         std::map<int, std::map<int, double>> flops;   // level -> tile -> flops
         std::map<int, double> level_flops;            // level -> FP32 flops

@@ -76,7 +76,8 @@ struct GettJob {
     int64_t n_inst;
     int64_t block0;                // first block of this job in the launch
     int32_t m_log, n_log, k_log;
-    int32_t split;                 // 1: a block per 2^rl x 2^cl outputs (long inner sums)
+    int32_t split;                 // 1: a block per 2^rl x 2^cl outputs (long inner sums); 2: a block per
+                                   // 64 outputs, a quarter of the sum per wave; 0: a thread per outputs
     int32_t rl, cl;                // split == 0: each thread computes 2^rl rows x 2^cl adjacent columns
     int32_t n_row_runs, n_col_runs;
     int32_t kc_log, pad_;
@@ -94,6 +95,22 @@ void set_launch_events(hipEvent_t start, hipEvent_t stop);
 // One launch for all jobs of a level: block b runs job d_block_job[b] & 0x7fffffff
 // (records in device memory), in FP64 when bit 31 is set, else in FP32.
 void launch_gett_group(const GettJob* d_jobs, const int32_t* d_block_job, int64_t blocks, hipStream_t s);
+
+// Consecutive small levels in one launch: block p walks part p's levels, level l
+// being blocks start[l] .. start[l + 1] - 1 of the list.  Parts are independent:
+// none reads or writes memory that another one writes.
+constexpr int kChainLevels = 24;
+struct GettChainPart {
+    int32_t n_levels;
+    uint32_t split_levels;         // bit l: level l has jobs whose sums are reduced over waves
+    int32_t start[kChainLevels + 1];
+};
+struct GettChainBlock {
+    const GettJob* job;
+    int64_t local;                 // block of the job
+    int32_t fp64, pad_;
+};
+void launch_gett_chain(const GettChainPart* d_parts, int n_parts, const GettChainBlock* d_blocks, hipStream_t s);
 
 // Grouped FP32 matrix-core contractions.  A job is one step: slices
 // i < n_inst with C_i = A_i B_i, operands in stored order (per-bit positions as
@@ -201,9 +218,9 @@ struct TailJob {
 };
 // d_part: blocks x (TN_MAX_LEVEL + 1) (sum, comp) pairs of scratch; the level
 // sums and the FP32 diagnostic value go res_shift bytes past the addresses in
-// the jobs (a results slot of a submitted estimate)
-void launch_tail(const TailJob* d_jobs, int n_jobs, int64_t blocks, int max_levels, double* d_part,
-                 int64_t res_shift, hipStream_t s);
+// the jobs (a results slot of a submitted estimate).  most_blocks: of one job.
+void launch_tail(const TailJob* d_jobs, int n_jobs, int64_t blocks, int64_t most_blocks, int max_levels,
+                 double* d_part, int64_t res_shift, hipStream_t s);
 
 // Neumaier level sums over contiguous ranges [start[u], start[u+1]).
 void launch_level_sum(const double* x, const int64_t* starts, int n_levels, double* out_sum_comp,

@@ -865,7 +865,11 @@ void k_mfma_group(const MfmaJob* __restrict__ jobs, const MfmaTile* __restrict__
 //               in registers, products added in inner-index order;
 //   split == 1: a block computes 2^rl x 2^cl outputs (long inner sums), each
 //               operand element read once for all of them, partial sums reduced
-//               in FP64 in a fixed order.
+//               in FP64 in a fixed order;
+//   split == 2: a block computes 64 outputs, each of its four waves a quarter of
+//               every chunk of the inner sum; the four partial sums are added in
+//               FP64 in order (few outputs, sums long enough that one thread's
+//               chain of loads is what the launch takes).
 // Bound: memory (L2 and HBM) for large steps, the chain of loads for small ones.
 // Against one output per thread and block with the record in LDS: 32 slices of
 // 2 x 2^19 over 4 terms 251 -> 116 us (302 MB), 1446 slices of 4 x 2 over 8192
@@ -924,8 +928,10 @@ __device__ __forceinline__ void vstore(TN_GLOBAL C2* p, const R (&re)[V], const 
 
 // One thread of a small step.  UNI: the block's outputs lie in one row group
 // of one slice, whose elements are then the same for every thread: scalar loads.
-template <typename R, typename C2, int RL, int CL, bool UNI>
-__device__ __forceinline__ void gett_rows(const TN_CONST GettJob* J, int64_t local, int tid) {
+// QUARTER: this thread's wave sums a quarter of the inner indices of its output
+// and leaves the partial sum in red.
+template <typename R, typename C2, int RL, int CL, bool UNI, bool QUARTER = false>
+__device__ __forceinline__ void gett_rows(const TN_CONST GettJob* J, int64_t local, int tid, double2* red = nullptr) {
     constexpr int RPT = 1 << RL, V = 1 << CL;
     constexpr int W = RPT * V * (sizeof(R) / 4);               // accumulated words / 2
     // inner indices whose loads are in flight together
@@ -934,7 +940,7 @@ __device__ __forceinline__ void gett_rows(const TN_CONST GettJob* J, int64_t loc
     const int m_log = J->m_log, n_log = J->n_log, k_log = J->k_log;
     const int mn_log = m_log + n_log;
     const int cw = n_log - CL;                                 // log2 column groups of a row group
-    const int64_t o = local * 256 + tid;
+    const int64_t o = QUARTER ? local * 64 + (tid & 63) : local * 256 + tid;
     if (!UNI && o >= (J->n_inst << (mn_log - RL - CL))) return;
     const int64_t c = (o & ((int64_t(1) << cw) - 1)) << CL;
     const int64_t rest = (UNI ? local * 256 : o) >> cw;
@@ -970,8 +976,9 @@ __device__ __forceinline__ void gett_rows(const TN_CONST GettJob* J, int64_t loc
         }
     };
     const int kc_log = J->kc_log;
-    const int kc = 1 << kc_log;
+    const int kc = QUARTER ? 1 << (kc_log - 2) : 1 << kc_log;
     const TN_CONST GettOff* kt = kc_log <= 3 ? J->k8 : cload<GettOff>(J->koff);
+    if (QUARTER) kt += __builtin_amdgcn_readfirstlane(tid >> 6) << (kc_log - 2);
     const TN_CONST GettStep* steps = cload<GettStep>(J->steps);
     const int64_t nh = int64_t(1) << (k_log - kc_log);
     int64_t ahh = 0, bhh = 0;
@@ -1026,18 +1033,20 @@ __device__ __forceinline__ void gett_rows(const TN_CONST GettJob* J, int64_t loc
         ahh += steps[t].a;
         bhh += steps[t].b;
     }
+    if constexpr (QUARTER) {
+        red[tid] = make_double2((double)sr[0][0], (double)si[0][0]);
+        return;
+    }
     TN_GLOBAL C2* Cp = gstore<C2>(J->C) + ((inst << mn_log) + (r0 << n_log) + c);
 #pragma unroll
     for (int i = 0; i < RPT; ++i) vstore<R, C2, V>(Cp + ((int64_t)i << n_log), sr[i], si[i]);
 }
 
-constexpr int kDotOut = 16;    // most outputs of a split block
-
 // A block's partial sums of 2^RL x 2^CL outputs: thread t takes inner indices
-// t + 256 h.  The wave's sums go to red[wave][output] (FP64, a fixed-order
+// t + 256 h.  The wave's sums go to red[64 wave + output] (FP64, a fixed-order
 // butterfly that halves the outputs a lane holds at each exchange).
 template <typename R, typename C2, int RL, int CL>
-__device__ __forceinline__ void gett_dot(const TN_CONST GettJob* J, int64_t local, int tid, double2 (*red)[kDotOut]) {
+__device__ __forceinline__ void gett_dot(const TN_CONST GettJob* J, int64_t local, int tid, double2* red) {
     constexpr int NR = 1 << RL, NC = 1 << CL, N = NR * NC;
     // U inner indices' loads are in flight together (NR + NC elements each)
     constexpr int U = (sizeof(R) == 4 ? 16 : 8) / (N == 1 ? 1 : N == 2 ? 2 : N == 4 ? (sizeof(R) == 4 ? 2 : 4)
@@ -1114,34 +1123,52 @@ __device__ __forceinline__ void gett_dot(const TN_CONST GettJob* J, int64_t loca
         vr[0] += __shfl_xor(vr[0], 32 >> s);
         vi[0] += __shfl_xor(vi[0], 32 >> s);
     }
-    if ((lane & ((64 >> NLOG) - 1)) == 0) red[tid >> 6][lane >> (6 - NLOG)] = make_double2(vr[0], vi[0]);
+    if ((lane & ((64 >> NLOG) - 1)) == 0) red[(tid >> 6) * 64 + (lane >> (6 - NLOG))] = make_double2(vr[0], vi[0]);
 }
 
 // after a barrier: the four waves' sums in order, one thread per output
 template <typename R, typename C2>
-__device__ __forceinline__ void gett_dot_finish(const TN_CONST GettJob* J, int64_t local, int tid,
-                                                const double2 (*red)[kDotOut]) {
+__device__ __forceinline__ void gett_finish(const TN_CONST GettJob* J, int64_t local, int tid, const double2* red) {
     const int rl = J->rl, cl = J->cl, n_log = J->n_log;
-    if (tid >= 1 << (rl + cl)) return;
-    const int tm = J->m_log - rl, tc = n_log - cl;
-    const int64_t inst = local >> (tm + tc);
-    const int64_t r = (((local >> tc) & ((int64_t(1) << tm) - 1)) << rl) + (tid >> cl);
-    const int64_t c = ((local & ((int64_t(1) << tc) - 1)) << cl) + (tid & ((1 << cl) - 1));
+    int64_t at;
+    if (J->split == 2) {
+        at = local * 64 + tid;
+        if (tid >= 64 || at >= (J->n_inst << (J->m_log + n_log))) return;
+    } else {
+        if (tid >= 1 << (rl + cl)) return;
+        const int tm = J->m_log - rl, tc = n_log - cl;
+        const int64_t inst = local >> (tm + tc);
+        const int64_t r = (((local >> tc) & ((int64_t(1) << tm) - 1)) << rl) + (tid >> cl);
+        const int64_t c = ((local & ((int64_t(1) << tc) - 1)) << cl) + (tid & ((1 << cl) - 1));
+        at = (((inst << J->m_log) + r) << n_log) + c;
+    }
     C2 out;
-    out.x = (R)(((red[0][tid].x + red[1][tid].x) + red[2][tid].x) + red[3][tid].x);
-    out.y = (R)(((red[0][tid].y + red[1][tid].y) + red[2][tid].y) + red[3][tid].y);
-    gst(gstore<C2>(J->C) + ((((inst << J->m_log) + r) << n_log) + c), out);
+    out.x = (R)(((red[tid].x + red[64 + tid].x) + red[128 + tid].x) + red[192 + tid].x);
+    out.y = (R)(((red[tid].y + red[64 + tid].y) + red[128 + tid].y) + red[192 + tid].y);
+    gst(gstore<C2>(J->C) + at, out);
 }
 
-// One 256-thread block of a job, up to the split sums' barrier.  SCALAR: the
-// row operand may be read with scalar loads (nothing in the launch writes it).
-template <typename R, typename C2, bool SCALAR>
-__device__ __forceinline__ void gett_block(const TN_CONST GettJob* J, int64_t local, int tid, double2 (*red)[kDotOut]) {
+// One 256-thread block of a job with one output per thread (per wave, per block),
+// up to the split sums' barrier; no scalar loads of operands.
+template <typename R, typename C2>
+__device__ __forceinline__ void gett_block_one(const TN_CONST GettJob* J, int64_t local, int tid, double2* red) {
+    if (J->split == 2) gett_rows<R, C2, 0, 0, false, true>(J, local, tid, red);
+    else if (J->split) gett_dot<R, C2, 0, 0>(J, local, tid, red);
+    else gett_rows<R, C2, 0, 0, false>(J, local, tid);
+}
+
+// The same for every job.  Rows that are the same for a whole block are read
+// with scalar loads (nothing in the launch writes them).
+template <typename R, typename C2>
+__device__ __forceinline__ void gett_block(const TN_CONST GettJob* J, int64_t local, int tid, double2* red) {
     constexpr bool F32 = sizeof(R) == 4;
     const int shape = J->rl * 4 + J->cl;
+    if (shape == 0 || J->split == 2) {
+        gett_block_one<R, C2>(J, local, tid, red);
+        return;
+    }
     if (J->split) {
         switch (shape) {
-        case 0: gett_dot<R, C2, 0, 0>(J, local, tid, red); break;
         case 1: gett_dot<R, C2, 0, 1>(J, local, tid, red); break;
         case 4: gett_dot<R, C2, 1, 0>(J, local, tid, red); break;
         case 5: gett_dot<R, C2, 1, 1>(J, local, tid, red); break;
@@ -1153,7 +1180,7 @@ __device__ __forceinline__ void gett_block(const TN_CONST GettJob* J, int64_t lo
         }
         return;
     }
-    if (SCALAR && J->n_log - J->cl >= 8) {
+    if (J->n_log - J->cl >= 8) {
         if constexpr (F32) switch (shape) {
         case 1: gett_rows<R, C2, 0, 1, true>(J, local, tid); return;
         case 5: gett_rows<R, C2, 1, 1, true>(J, local, tid); return;
@@ -1168,7 +1195,6 @@ __device__ __forceinline__ void gett_block(const TN_CONST GettJob* J, int64_t lo
         }
     }
     switch (shape) {
-    case 0: gett_rows<R, C2, 0, 0, false>(J, local, tid); break;
     case 4: gett_rows<R, C2, 1, 0, false>(J, local, tid); break;
     case 8: gett_rows<R, C2, 2, 0, false>(J, local, tid); break;
     case 12: gett_rows<R, C2, 3, 0, false>(J, local, tid); break;
@@ -1186,17 +1212,70 @@ __device__ __forceinline__ void gett_block(const TN_CONST GettJob* J, int64_t lo
 // host, so a block finds its job with one load.
 __global__ __launch_bounds__(256, 4) void k_gett_group(const GettJob* __restrict__ jobs,
                                                        const int32_t* __restrict__ block_job) {
-    __shared__ double2 red[4][kDotOut];
+    __shared__ double2 red[256];
     const uint32_t e = (uint32_t)cload<int32_t>(block_job)[blockIdx.x];
     const TN_CONST GettJob* J = cload<GettJob>(jobs) + (e & 0x7fffffffu);
     const int64_t local = (int64_t)blockIdx.x - J->block0;
     const int tid = (int)threadIdx.x;
-    if (e >> 31) gett_block<double, double2, true>(J, local, tid, red);
-    else gett_block<float, float2, true>(J, local, tid, red);
+    if (e >> 31) gett_block<double, double2>(J, local, tid, red);
+    else gett_block<float, float2>(J, local, tid, red);
     if (!J->split) return;
     __syncthreads();
-    if (e >> 31) gett_dot_finish<double, double2>(J, local, tid, red);
-    else gett_dot_finish<float, float2>(J, local, tid, red);
+    if (e >> 31) gett_finish<double, double2>(J, local, tid, red);
+    else gett_finish<float, float2>(J, local, tid, red);
+}
+
+// Consecutive small levels in one launch.  The launch's blocks are the
+// independent parts of those levels (no part touches memory that another one
+// writes): a block of four 256-thread groups walks its part's levels, four
+// 256-thread blocks of a level at a time, with a barrier after each level, so no
+// block waits for another.  The values of a level are read back by the same
+// block through the L1 that it wrote them through; only records and tables
+// (written by no block) use scalar loads.
+//   Bound: the chain of loads of each level, about 1.2 us with its records in
+//   the caches (8-qubit chain: its three levels 5.3 us; as launches 3.4 + 3.2 +
+//   3.5 us and the gaps between them), 3 to 4 us in the first pass over a schedule.
+__global__ __launch_bounds__(1024) void k_gett_chain(const GettChainPart* __restrict__ parts,
+                                                     const GettChainBlock* __restrict__ blocks) {
+    __shared__ double2 red[2][1024];
+    const TN_CONST GettChainPart* P = cload<GettChainPart>(parts) + blockIdx.x;
+    const TN_CONST GettChainBlock* list = cload<GettChainBlock>(blocks);
+    const int grp = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8), tid = (int)threadIdx.x & 255;
+    const int nl = P->n_levels, last = P->start[nl] - 1;
+    const uint32_t split_levels = P->split_levels;
+    // the record of this group's next block is read during the current one
+    const TN_CONST GettChainBlock* B = list + (P->start[0] + grp < last ? P->start[0] + grp : last);
+    const TN_CONST GettJob* J = cload<GettJob>(B->job);
+    int64_t local = B->local;
+    int wide = B->fp64, par = 0;
+    for (int l = 0; l < nl; ++l) {
+        const int at = P->start[l], n = P->start[l + 1] - at;
+        const bool split = split_levels >> l & 1;
+        if (l) __syncthreads();                // the level before is written
+        for (int v = 0; v < n; v += 4, par ^= 1) {
+            const bool mine = v + grp < n;
+            const int next = (v + 4 < n ? at + v + 4 : at + n) + grp;
+            const TN_CONST GettChainBlock* Bn = list + (next < last ? next : last);
+            const TN_CONST GettJob* Jn = cload<GettJob>(Bn->job);
+            const int64_t local_n = Bn->local;
+            const int wide_n = Bn->fp64;
+            double2* r = red[par] + 256 * grp;
+            if (mine) {
+                if (wide) gett_block_one<double, double2>(J, local, tid, r);
+                else gett_block_one<float, float2>(J, local, tid, r);
+            }
+            if (split) {
+                __syncthreads();               // (the other buffer's sums were finished before it)
+                if (mine && J->split) {
+                    if (wide) gett_finish<double, double2>(J, local, tid, r);
+                    else gett_finish<float, float2>(J, local, tid, r);
+                }
+            }
+            J = Jn;
+            local = local_n;
+            wide = wide_n;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1873,14 +1952,17 @@ __global__ __launch_bounds__(256) void k_level_sum(const double* x, const int64_
     level_sum_block(x, starts, out, blockIdx.x);
 }
 
-// The tail of all packed circuits in two launches.  k_tail_terms: block b
-// finalizes terms 256 (b - block0) ... of its circuit (X_t = w |a_t|^2 and a_t
-// written to the per-term outputs) and writes, for every level u, the
-// Neumaier pair of its terms of
-// level u (a fixed tree over the block's lanes) to part[b][u].
-// k_tail_sums: block (circuit, u) adds the circuit's block pairs of level u in
-// block order (strided per lane, then a fixed tree): deterministic.
-__device__ __forceinline__ int tail_job_of(const TailJob* __restrict__ jobs, int n_jobs, int64_t b) {
+// The tail of all packed circuits: 256 terms at a time are finalized
+// (X_t = w |a_t|^2 and a_t written to the per-term outputs) and, for every level
+// u, the Neumaier pair of their terms of level u is formed by a fixed tree over
+// the lanes; a circuit's pairs of level u are then added in block order (again a
+// fixed tree): deterministic.  Circuits of up to 8 blocks run in one launch, one
+// block per circuit (k_tail_small: 1771 terms in two rounds of four blocks);
+// larger ones as k_tail_terms, which leaves the pairs in part[block][u], and
+// k_tail_sums.  Both orders are the same, so the sums do not depend on the form.
+constexpr int kTailSmallBlocks = 8;
+
+__device__ __forceinline__ int tail_job_of(const TN_CONST TailJob* jobs, int n_jobs, int64_t b) {
     int lo = 0, hi = n_jobs - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -1890,113 +1972,125 @@ __device__ __forceinline__ int tail_job_of(const TailJob* __restrict__ jobs, int
     return lo;
 }
 
-// Finalize of one block of 256 terms (FP64): amplitude = scalar * prod of the
-// term's cluster values in cluster order, X = w |amplitude|^2 (a doubled
-// network's value is the amplitude itself: X = w Re(amplitude)).  The term
-// `zero_term` takes its cluster values from the FP64 roots, and its product
-// over the FP32 roots goes to the results as a diagnostic.  The clusters' root
-// addresses are staged in LDS (kFinPtrs per round), and each thread loads
-// kFinBatch cluster indices, then their values, before multiplying, so a term
-// costs two dependent loads per batch.
+// Finalize of one term (FP64): amplitude = scalar * prod of the term's cluster
+// values in cluster order, X = w |amplitude|^2 (a doubled network's value is the
+// amplitude itself: X = w Re(amplitude)).  The term `zero_term` takes its
+// cluster values from the FP64 roots, and its product over the FP32 roots goes
+// to the results as a diagnostic.  Each thread loads kFinBatch cluster indices,
+// then their values, before multiplying, so a term costs two dependent loads
+// per batch; the root addresses are scalar loads.  Returns X (0: not live).
 constexpr int kFinBatch = 8;
-constexpr int kFinPtrs = 64;
+
+__device__ __forceinline__ double tail_term(const TN_CONST FinalizeArgs* f, int64_t t, int64_t res_shift) {
+    if (t >= f->n_terms) return 0.0;
+    const int32_t li = gload<int32_t>(f->live_index)[t];
+    if (li < 0) {
+        gstore<double>(f->x_out)[t] = 0.0;
+        gst(gstore<float2>(f->amp_out) + t, make_float2(0.0f, 0.0f));
+        return 0.0;
+    }
+    const double wt = gload<double>(f->w)[t];
+    const bool hi = t == f->zero_term;
+    const int ncl = f->n_clusters;
+    const TN_GLOBAL int32_t* ri = gload<int32_t>(f->root_idx) + (int64_t)li * ncl;
+    const TN_CONST int64_t* rp32 = cload<int64_t>(f->root_ptrs);
+    const TN_CONST int64_t* rp64 = cload<int64_t>(f->root64_ptrs);
+    double ar = f->scalar_re, ai = f->scalar_im;      // over the FP32 roots
+    double hr = ar, hm = ai;                          // over the FP64 roots (zero_term)
+    for (int c0 = 0; c0 < ncl; c0 += kFinBatch) {
+        int32_t j[kFinBatch];
+        float2 v[kFinBatch];
+        // loads past the last cluster repeat it (in bounds, not used):
+        // unconditional loads are all issued before the first wait
+#pragma unroll
+        for (int q = 0; q < kFinBatch; ++q) j[q] = ri[c0 + q < ncl ? c0 + q : ncl - 1];
+#pragma unroll
+        for (int q = 0; q < kFinBatch; ++q)
+            v[q] = gld(gload<float2>((const void*)rp32[c0 + q < ncl ? c0 + q : ncl - 1]) + j[q]);
+#pragma unroll
+        for (int q = 0; q < kFinBatch; ++q)
+            if (c0 + q < ncl) {
+                const double vr = (double)v[q].x, vi = (double)v[q].y;
+                const double nr = ar * vr - ai * vi;
+                const double ni = ar * vi + ai * vr;
+                ar = nr;
+                ai = ni;
+            }
+        if (hi) {
+            double2 w[kFinBatch];
+#pragma unroll
+            for (int q = 0; q < kFinBatch; ++q)
+                w[q] = gld(gload<double2>((const void*)rp64[c0 + q < ncl ? c0 + q : ncl - 1]) + j[q]);
+#pragma unroll
+            for (int q = 0; q < kFinBatch; ++q)
+                if (c0 + q < ncl) {
+                    const double nr = hr * w[q].x - hm * w[q].y;
+                    const double ni = hr * w[q].y + hm * w[q].x;
+                    hr = nr;
+                    hm = ni;
+                }
+        }
+    }
+    const double pr = hi ? hr : ar, pi = hi ? hm : ai;
+    const double x = wt * (f->re_value ? pr : pr * pr + pi * pi);
+    gstore<double>(f->x_out)[t] = x;
+    gst(gstore<float2>(f->amp_out) + t, make_float2((float)pr, (float)pi));
+    if (hi && f->x0_fp32_out) *(double*)((char*)f->x0_fp32_out + res_shift) = wt * (f->re_value ? ar : ar * ar + ai * ai);
+    return x;
+}
+
+// Neumaier pairs of a wave's terms t (value x), per level, to pairs[u][wave].
+struct TailPairs {
+    double s[TN_MAX_LEVEL + 1][4], c[TN_MAX_LEVEL + 1][4];
+};
+__device__ __forceinline__ void tail_wave_pairs(const TN_CONST TailJob* J, int64_t t, double x, int wave,
+                                                TailPairs& out) {
+    const TN_CONST int64_t* starts = cload<int64_t>(J->starts);
+    const int64_t t0 = t & ~int64_t(63);                   // the wave's first term
+    for (int u = 0; u < J->n_levels; ++u) {
+        const int64_t lb = starts[u], le = starts[u + 1];
+        double s = 0.0, c = 0.0;
+        if (le > t0 && lb < t0 + 64) {
+            s = t >= lb && t < le ? x : 0.0;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                const double s2 = __shfl_xor(s, off), c2 = __shfl_xor(c, off);
+                c += c2;
+                neumaier_add(s, c, s2);
+            }
+        }
+        if ((threadIdx.x & 63) == 0) {
+            out.s[u][wave] = s;
+            out.c[u][wave] = c;
+        }
+    }
+}
+// the four waves' pairs of level u in order
+__device__ __forceinline__ void tail_block_pair(const TailPairs& p, int u, double& s, double& c) {
+    s = p.s[u][0];
+    c = p.c[u][0];
+#pragma unroll
+    for (int q = 1; q < 4; ++q) {
+        c += p.c[u][q];
+        neumaier_add(s, c, p.s[u][q]);
+    }
+}
 
 __global__ __launch_bounds__(256) void k_tail_terms(const TailJob* __restrict__ jobs, int n_jobs,
                                                     double* __restrict__ part, int64_t res_shift) {
-    __shared__ double ss[256];
-    __shared__ double cc[256];
-    __shared__ const TN_GLOBAL float2* rp32[kFinPtrs];
-    __shared__ const TN_GLOBAL double2* rp64[kFinPtrs];
+    __shared__ TailPairs pairs;
     const int64_t b = blockIdx.x;
-    const TailJob& J = jobs[tail_job_of(jobs, n_jobs, b)];
-    const FinalizeArgs& f = J.f;
-    const int64_t t0 = (b - J.block0) * 256;
-    const int64_t t = t0 + threadIdx.x;
-    const bool in = t < f.n_terms;
-    const int32_t li = in ? gload<int32_t>(f.live_index)[t] : -1;
-    const bool hi = in && t == f.zero_term;
-    const int ncl = f.n_clusters;
-    const TN_GLOBAL int32_t* __restrict__ ri = gload<int32_t>(f.root_idx) + (int64_t)(li < 0 ? 0 : li) * ncl;
-    double ar = f.scalar_re, ai = f.scalar_im;      // over the FP32 roots
-    double hr = ar, hm = ai;                        // over the FP64 roots (zero_term)
-    for (int c0 = 0; c0 < ncl; c0 += kFinPtrs) {
-        const int nc = ncl - c0 < kFinPtrs ? ncl - c0 : kFinPtrs;
-        __syncthreads();                            // the previous round's addresses are read
-        if ((int)threadIdx.x < nc) {            // (FP64 addresses are 0 without the FP64 pass)
-            const int64_t a32 = gload<int64_t>(f.root_ptrs)[c0 + threadIdx.x];
-            const int64_t a64 = gload<int64_t>(f.root64_ptrs)[c0 + threadIdx.x];
-            rp32[threadIdx.x] = gload<float2>((const void*)a32);
-            rp64[threadIdx.x] = gload<double2>((const void*)a64);
-        }
-        __syncthreads();
-        if (li < 0) continue;
-        for (int q0 = 0; q0 < nc; q0 += kFinBatch) {
-            int32_t j[kFinBatch];
-            float2 v[kFinBatch];
-            // loads past the round's last cluster repeat it (in bounds, not used):
-            // unconditional loads are all issued before the first wait
-#pragma unroll
-            for (int q = 0; q < kFinBatch; ++q) j[q] = ri[c0 + (q0 + q < nc ? q0 + q : nc - 1)];
-#pragma unroll
-            for (int q = 0; q < kFinBatch; ++q) v[q] = gld(rp32[q0 + q < nc ? q0 + q : nc - 1] + j[q]);
-#pragma unroll
-            for (int q = 0; q < kFinBatch; ++q)
-                if (q0 + q < nc) {
-                    const double vr = (double)v[q].x, vi = (double)v[q].y;
-                    const double nr = ar * vr - ai * vi;
-                    const double ni = ar * vi + ai * vr;
-                    ar = nr;
-                    ai = ni;
-                }
-            if (hi) {
-                double2 w[kFinBatch];
-#pragma unroll
-                for (int q = 0; q < kFinBatch; ++q) w[q] = gld(rp64[q0 + q < nc ? q0 + q : nc - 1] + j[q]);
-#pragma unroll
-                for (int q = 0; q < kFinBatch; ++q)
-                    if (q0 + q < nc) {
-                        const double nr = hr * w[q].x - hm * w[q].y;
-                        const double ni = hr * w[q].y + hm * w[q].x;
-                        hr = nr;
-                        hm = ni;
-                    }
-            }
-        }
-    }
-    double x = 0.0;
-    if (in) {
-        if (li < 0) {
-            f.x_out[t] = 0.0;
-            f.amp_out[2 * t] = 0.0f;
-            f.amp_out[2 * t + 1] = 0.0f;
-        } else {
-            const double pr = hi ? hr : ar, pi = hi ? hm : ai;
-            const double wt = f.w[t];
-            x = wt * (f.re_value ? pr : pr * pr + pi * pi);
-            f.x_out[t] = x;
-            f.amp_out[2 * t] = (float)pr;
-            f.amp_out[2 * t + 1] = (float)pi;
-            if (hi && f.x0_fp32_out)
-                *(double*)((char*)f.x0_fp32_out + res_shift) = wt * (f.re_value ? ar : ar * ar + ai * ai);
-        }
-    }
-    const int64_t t_end = t0 + 256 < f.n_terms ? t0 + 256 : f.n_terms;
-    double* out = part + b * (2 * (TN_MAX_LEVEL + 1));
-    for (int u = 0; u < J.n_levels; ++u) {
-        const int64_t lb = J.starts[u], le = J.starts[u + 1];
-        if (le <= t0 || lb >= t_end) {           // no term of this block has level u
-            if (threadIdx.x == 0) {
-                out[2 * u] = 0.0;
-                out[2 * u + 1] = 0.0;
-            }
-            continue;
-        }
-        double sv = (t >= lb && t < le) ? x : 0.0, cv = 0.0;
-        neumaier_block_shfl<256>(sv, cv, ss, cc);
-        if (threadIdx.x == 0) {
-            out[2 * u] = sv;
-            out[2 * u + 1] = cv;
-        }
+    const TN_CONST TailJob* J = cload<TailJob>(jobs) + tail_job_of(cload<TailJob>(jobs), n_jobs, b);
+    const int64_t t = (b - J->block0) * 256 + threadIdx.x;
+    const double x = tail_term(&J->f, t, res_shift);
+    tail_wave_pairs(J, t, x, __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), pairs);
+    __syncthreads();
+    if ((int)threadIdx.x < J->n_levels) {
+        double s, c;
+        tail_block_pair(pairs, (int)threadIdx.x, s, c);
+        double* out = part + b * (2 * (TN_MAX_LEVEL + 1)) + 2 * threadIdx.x;
+        out[0] = s;
+        out[1] = c;
     }
 }
 
@@ -2004,21 +2098,52 @@ __global__ __launch_bounds__(256) void k_tail_sums(const TailJob* __restrict__ j
                                                    int64_t res_shift) {
     __shared__ double ss[256];
     __shared__ double cc[256];
-    const TailJob J = jobs[blockIdx.x];
+    const TN_CONST TailJob* J = cload<TailJob>(jobs) + blockIdx.x;
     const int u = blockIdx.y;
-    if (u >= J.n_levels) return;
-    const int64_t nb = (J.f.n_terms + 255) / 256;
+    if (u >= J->n_levels) return;
+    const int64_t nb = (J->f.n_terms + 255) / 256;
     double s = 0.0, c = 0.0;
     for (int64_t q = threadIdx.x; q < nb; q += 256) {
-        const double* pr = part + (J.block0 + q) * (2 * (TN_MAX_LEVEL + 1)) + 2 * u;
+        const double* pr = part + (J->block0 + q) * (2 * (TN_MAX_LEVEL + 1)) + 2 * u;
         neumaier_add(s, c, pr[0]);
         c += pr[1];
     }
     neumaier_block_shfl<256>(s, c, ss, cc);
     if (threadIdx.x == 0) {
-        double* sums = (double*)((char*)J.sums + res_shift);
+        double* sums = (double*)((char*)J->sums + res_shift);
         sums[2 * u] = s + c;
         sums[2 * u + 1] = c;
+    }
+}
+
+// One block per circuit of at most kTailSmallBlocks blocks of terms: four
+// 256-thread groups take a block each, then wave u adds the blocks' pairs of
+// level u in the order of k_tail_sums.
+__global__ __launch_bounds__(1024) void k_tail_small(const TailJob* __restrict__ jobs, int64_t res_shift) {
+    __shared__ TailPairs pairs[kTailSmallBlocks];
+    const TN_CONST TailJob* J = cload<TailJob>(jobs) + blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int nb = (int)((J->f.n_terms + 255) / 256);
+    for (int b = wave >> 2; b < nb; b += 4) {
+        const int64_t t = (int64_t)b * 256 + (threadIdx.x & 255);
+        const double x = tail_term(&J->f, t, res_shift);
+        tail_wave_pairs(J, t, x, wave & 3, pairs[b]);
+    }
+    __syncthreads();
+    if (wave >= J->n_levels) return;
+    const int lane = (int)threadIdx.x & 63;
+    double s = 0.0, c = 0.0;
+    if (lane < nb) tail_block_pair(pairs[lane], wave, s, c);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const double s2 = __shfl_xor(s, off), c2 = __shfl_xor(c, off);
+        c += c2;
+        neumaier_add(s, c, s2);
+    }
+    if (lane == 0) {
+        double* sums = (double*)((char*)J->sums + res_shift);
+        sums[2 * wave] = s + c;
+        sums[2 * wave + 1] = c;
     }
 }
 
@@ -2138,6 +2263,10 @@ void launch_gett_group(const GettJob* d_jobs, const int32_t* d_block_job, int64_
     launch_k(k_gett_group, dim3((unsigned)blocks), dim3(256), s, d_jobs, d_block_job);
 }
 
+void launch_gett_chain(const GettChainPart* d_parts, int n_parts, const GettChainBlock* d_blocks, hipStream_t s) {
+    launch_k(k_gett_chain, dim3((unsigned)n_parts), dim3(1024), s, d_parts, d_blocks);
+}
+
 static void launch_mfma_tile(const TileCfg& t, const GemmArgs& g, hipStream_t s, bool gather) {
     const int64_t ntiles = std::max<int64_t>(1, (int64_t(1) << g.n_log) / t.bnc);
     const int64_t tiles = ((int64_t(1) << g.m_log) / t.bm) * ntiles;
@@ -2226,11 +2355,14 @@ void launch_level_sum(const double* x, const int64_t* starts, int n_levels, doub
     hipLaunchKernelGGL(k_level_sum, dim3(n_levels), dim3(256), 0, s, x, starts, out);
 }
 
-void launch_tail(const TailJob* d_jobs, int n_jobs, int64_t blocks, int max_levels, double* d_part,
-                 int64_t res_shift, hipStream_t s) {
+void launch_tail(const TailJob* d_jobs, int n_jobs, int64_t blocks, int64_t most_blocks, int max_levels,
+                 double* d_part, int64_t res_shift, hipStream_t s) {
     if (n_jobs == 0) return;
-    if (blocks > 0)
-        hipLaunchKernelGGL(k_tail_terms, dim3((unsigned)blocks), dim3(256), 0, s, d_jobs, n_jobs, d_part, res_shift);
+    if (most_blocks <= kTailSmallBlocks) {
+        hipLaunchKernelGGL(k_tail_small, dim3((unsigned)n_jobs), dim3(1024), 0, s, d_jobs, res_shift);
+        return;
+    }
+    hipLaunchKernelGGL(k_tail_terms, dim3((unsigned)blocks), dim3(256), 0, s, d_jobs, n_jobs, d_part, res_shift);
     hipLaunchKernelGGL(k_tail_sums, dim3((unsigned)n_jobs, (unsigned)max_levels), dim3(256), 0, s, d_jobs,
                        (const double*)d_part, res_shift);
 }
