@@ -238,6 +238,14 @@ template <typename T>
 __device__ __forceinline__ TN_GLOBAL T* gstore(void* p) {
     return (TN_GLOBAL T*)p;
 }
+#define TN_CONST __attribute__((address_space(4)))
+// read-only view of memory that no block of the launch writes: uniform
+// addresses become scalar loads
+template <typename T>
+__device__ __forceinline__ const TN_CONST T* cload(const void* p) {
+    return (const TN_CONST T*)p;
+}
+
 // element loads from global views (HIP's vector types do not copy across
 // address spaces): one 8-byte load for complex64, two for complex128
 __device__ __forceinline__ float2 gld(const TN_GLOBAL float2* p) {
@@ -278,23 +286,43 @@ __device__ __forceinline__ int64_t deposit(int64_t x, const int8_t* pos, int lo,
     return o;
 }
 
+// the same from a record in constant memory
+__device__ __forceinline__ int64_t deposit(int64_t x, const TN_CONST int8_t* pos, int lo, int hi) {
+    const TN_CONST uint32_t* pw = (const TN_CONST uint32_t*)pos;
+    int64_t o = 0;
+#pragma unroll
+    for (int j = 0; j < 32; ++j) {
+        if (j >= hi) break;
+        if (j >= lo) o |= (int64_t)((x >> j) & 1) << (int)((pw[j >> 2] >> (8 * (j & 3))) & 63u);
+    }
+    return o;
+}
+
 // Offset steps of a chunk counter: with chunk index h (inner index h << lo),
 // deposit(h + 1) = deposit(h) + step[ctz(~h)], where step[t] is the offset of
 // inner bit lo + t minus the offsets of the bits below it, lo <= bit < lo + t.
-// Filled by the first threads of a block; t < 32.
-__device__ __forceinline__ void chunk_steps(const int8_t* pos, int lo, int hi, int64_t* step) {
-    for (int t = threadIdx.x; t < hi - lo; t += blockDim.x) {
-        int64_t below = 0;
-        for (int j = 0; j < t; ++j) below += int64_t(1) << pos[lo + j];
-        step[t] = (int64_t(1) << pos[lo + t]) - below;
+// The sums run in scalar registers; thread t writes entry t (t < 32).  (Placing
+// the whole counter anew for each chunk instead cost long tiles 7 %.)
+__device__ __forceinline__ void chunk_steps(const TN_CONST int8_t* pos, int lo, int hi, int64_t* step) {
+    const TN_CONST uint32_t* pw = (const TN_CONST uint32_t*)pos;
+    int64_t below = 0, mine = 0;
+#pragma unroll
+    for (int j = 0; j < 32; ++j) {
+        if (j >= hi) break;
+        if (j < lo) continue;
+        const int64_t at = int64_t(1) << ((pw[j >> 2] >> (8 * (j & 3))) & 63u);
+        if ((int)threadIdx.x == j - lo) mine = at - below;
+        below += at;
     }
+    if ((int)threadIdx.x < hi - lo) step[threadIdx.x] = mine;
 }
 
 // Output offset (element index into C) of row i / column j of a grouped tile,
 // -1 for padding: merge 2 stacks `cnt` slices along the rows, merge 1 along
 // the columns, merge 0 holds one slice at origin (tm0, tn0).  Shared by the
 // tile kernels and the split-sum reduction, so both address the same outputs.
-__device__ __forceinline__ int64_t tile_out_row(const MfmaJob& J, const MfmaTile& T, int i) {
+template <typename Job>
+__device__ __forceinline__ int64_t tile_out_row(const Job& J, const MfmaTile& T, int i) {
     const int m_log = J.m_log;
     const int64_t m = int64_t(1) << m_log, n = int64_t(1) << J.n_log;
     if (J.merge == 2) {
@@ -304,7 +332,8 @@ __device__ __forceinline__ int64_t tile_out_row(const MfmaJob& J, const MfmaTile
     const int64_t r = T.tm0 + i;
     return r < m ? (J.merge == 1 ? 0 : gload<int64_t>(J.oc)[T.s0]) + r * n : -1;
 }
-__device__ __forceinline__ int64_t tile_out_col(const MfmaJob& J, const MfmaTile& T, int j) {
+template <typename Job>
+__device__ __forceinline__ int64_t tile_out_col(const Job& J, const MfmaTile& T, int j) {
     const int n_log = J.n_log;
     const int64_t n = int64_t(1) << n_log;
     if (J.merge == 1) {
@@ -313,6 +342,42 @@ __device__ __forceinline__ int64_t tile_out_col(const MfmaJob& J, const MfmaTile
     }
     const int64_t c = T.tn0 + j;
     return c < n ? c : -1;
+}
+
+// Offset tables of a grouped tile: A / B element offsets of its rows and columns
+// and of the inner indices of a chunk, C offsets of its rows and columns (-1 =
+// padding).  One entry per thread where the block has that many; the job record
+// is read with scalar loads.  (With the record copied to LDS by one thread and
+// the step tables summed entry by entry, a FP64 level of 131072 tiles of k = 16
+// took 741 us, now 597; 65536 of k = 32 617 -> 518; the 12 packed circuits 2196
+// -> 2092 us.)
+template <int BM, int BN, int BK, int NT>
+__device__ __forceinline__ void tile_tables(const TN_CONST MfmaJob& J, const MfmaTile& T, int kc_log, int64_t* row_a,
+                                            int64_t* row_c, int64_t* col_b, int64_t* col_c, int64_t* ak_lo,
+                                            int64_t* bk_lo) {
+    const int m_log = J.m_log, n_log = J.n_log;
+    const int64_t m = int64_t(1) << m_log, n = int64_t(1) << n_log;
+    const int merge = J.merge, kc = 1 << kc_log;
+    for (int e = threadIdx.x; e < BM + BN + BK; e += NT) {
+        if (e < BM) {
+            const int seg = merge == 2 ? e >> m_log : 0;
+            const int64_t r = merge == 2 ? e & (m - 1) : T.tm0 + e;
+            const bool ok = merge == 2 ? seg < T.cnt : r < m;
+            row_a[e] = ok ? gload<int64_t>(J.oa)[T.s0 + seg] + deposit(r, J.a_row, 0, m_log) : -1;
+            row_c[e] = tile_out_row(J, T, e);
+        } else if (e < BM + BN) {
+            const int j = e - BM;
+            const int seg = merge == 1 ? j >> n_log : 0;
+            const int64_t c = merge == 1 ? j & (n - 1) : T.tn0 + j;
+            const bool ok = merge == 1 ? seg < T.cnt : c < n;
+            col_b[j] = ok ? gload<int64_t>(J.ob)[T.s0 + seg] + deposit(c, J.b_col, 0, n_log) : -1;
+            col_c[j] = tile_out_col(J, T, j);
+        } else {
+            const int i = e - BM - BN;
+            ak_lo[i] = i < kc ? deposit(i, J.a_k, 0, kc_log) : 0;
+            bk_lo[i] = i < kc ? deposit(i, J.b_k, 0, kc_log) : 0;
+        }
+    }
 }
 
 template <int BM, int BNC>
@@ -577,44 +642,15 @@ void k_mfma_group(const MfmaJob* __restrict__ jobs, const MfmaTile* __restrict__
     __shared__ __align__(16) float Bs[2 * BBUF];
     __shared__ int64_t row_a[BM], row_c[BM], col_b[BNC], col_c[BNC], ak_lo[BKC], bk_lo[BKC];
     __shared__ int64_t a_step[32], b_step[32];
-    __shared__ MfmaJob J;
     const MfmaTile T = tiles[blockIdx.x];
-    if (threadIdx.x == 0) J = jobs[T.job];
-    __syncthreads();
-    const int m_log = J.m_log, n_log = J.n_log, k_log = J.k_log;
-    const int64_t m = int64_t(1) << m_log, n = int64_t(1) << n_log, k = int64_t(1) << k_log;
+    const TN_CONST MfmaJob& J = cload<MfmaJob>(jobs)[T.job];
+    const int k_log = J.k_log;
+    const int64_t k = int64_t(1) << k_log;
     const int kc = k < BKC ? (int)k : BKC;
     const int kc_log = k_log < BKC_LOG ? k_log : BKC_LOG;
-    for (int i = threadIdx.x; i < BM; i += NT) {
-        int64_t ra = -1;
-        if (J.merge == 2) {
-            const int seg = i >> m_log;
-            if (seg < T.cnt) ra = gload<int64_t>(J.oa)[T.s0 + seg] + deposit(i & (m - 1), J.a_row, 0, m_log);
-        } else {
-            const int64_t r = T.tm0 + i;
-            if (r < m) ra = gload<int64_t>(J.oa)[T.s0] + deposit(r, J.a_row, 0, m_log);
-        }
-        row_a[i] = ra;
-        row_c[i] = tile_out_row(J, T, i);
-    }
-    for (int j = threadIdx.x; j < BNC; j += NT) {
-        int64_t cb = -1;
-        if (J.merge == 1) {
-            const int seg = j >> n_log;
-            if (seg < T.cnt) cb = gload<int64_t>(J.ob)[T.s0 + seg] + deposit(j & (n - 1), J.b_col, 0, n_log);
-        } else {
-            const int64_t c = T.tn0 + j;
-            if (c < n) cb = gload<int64_t>(J.ob)[T.s0] + deposit(c, J.b_col, 0, n_log);
-        }
-        col_b[j] = cb;
-        col_c[j] = tile_out_col(J, T, j);
-    }
-    for (int i = threadIdx.x; i < BKC; i += NT) {
-        ak_lo[i] = i < kc ? deposit(i, J.a_k, 0, kc_log) : 0;
-        bk_lo[i] = i < kc ? deposit(i, J.b_k, 0, kc_log) : 0;
-    }
     chunk_steps(J.a_k, kc_log, k_log, a_step);
     chunk_steps(J.b_k, kc_log, k_log, b_step);
+    tile_tables<BM, BNC, BKC, NT>(J, T, kc_log, row_a, row_c, col_b, col_c, ak_lo, bk_lo);
     __syncthreads();
     const TN_GLOBAL float2* __restrict__ A = gload<float2>(J.A);
     const TN_GLOBAL float2* __restrict__ B = gload<float2>(J.B);
@@ -876,14 +912,6 @@ void k_mfma_group(const MfmaJob* __restrict__ jobs, const MfmaTile* __restrict__
 // terms 207 -> 82 us, 352 of 4 x 4 over 16384 102 -> 54 us, a level of 8 x 8
 // sums of 1024 terms 12.4 -> 6.0 us.
 // ---------------------------------------------------------------------------
-#define TN_CONST __attribute__((address_space(4)))
-// read-only view of memory that no block of the launch writes: uniform
-// addresses become scalar loads
-template <typename T>
-__device__ __forceinline__ const TN_CONST T* cload(const void* p) {
-    return (const TN_CONST T*)p;
-}
-
 __device__ __forceinline__ int64_t run_offset(const TN_CONST uint32_t* runs, int n, uint32_t x) {
     int64_t o = 0;
     for (int i = 0; i < n; ++i) {
@@ -1428,44 +1456,15 @@ __global__ __launch_bounds__(256) void k_tile64_group(const MfmaJob* __restrict_
     __shared__ double2 Bs2[2][BK][BN + 2];
     __shared__ int64_t row_a[BM], row_c[BM], col_b[BN], col_c[BN], ak_lo[BK], bk_lo[BK];
     __shared__ int64_t a_step[32], b_step[32];
-    __shared__ MfmaJob J;
     const MfmaTile T = tiles[blockIdx.x];
-    if (threadIdx.x == 0) J = jobs[T.job];
-    __syncthreads();
-    const int m_log = J.m_log, n_log = J.n_log, k_log = J.k_log;
-    const int64_t m = int64_t(1) << m_log, n = int64_t(1) << n_log, k = int64_t(1) << k_log;
+    const TN_CONST MfmaJob& J = cload<MfmaJob>(jobs)[T.job];
+    const int k_log = J.k_log;
+    const int64_t k = int64_t(1) << k_log;
     const int kc = k < BK ? (int)k : BK;
     const int kc_log = k_log < BK_LOG ? k_log : BK_LOG;
-    for (int i = threadIdx.x; i < BM; i += 256) {
-        int64_t ra = -1;
-        if (J.merge == 2) {
-            const int seg = i >> m_log;
-            if (seg < T.cnt) ra = gload<int64_t>(J.oa)[T.s0 + seg] + deposit(i & (m - 1), J.a_row, 0, m_log);
-        } else {
-            const int64_t r = T.tm0 + i;
-            if (r < m) ra = gload<int64_t>(J.oa)[T.s0] + deposit(r, J.a_row, 0, m_log);
-        }
-        row_a[i] = ra;
-        row_c[i] = tile_out_row(J, T, i);
-    }
-    for (int j = threadIdx.x; j < BN; j += 256) {
-        int64_t cb = -1;
-        if (J.merge == 1) {
-            const int seg = j >> n_log;
-            if (seg < T.cnt) cb = gload<int64_t>(J.ob)[T.s0 + seg] + deposit(j & (n - 1), J.b_col, 0, n_log);
-        } else {
-            const int64_t c = T.tn0 + j;
-            if (c < n) cb = gload<int64_t>(J.ob)[T.s0] + deposit(c, J.b_col, 0, n_log);
-        }
-        col_b[j] = cb;
-        col_c[j] = tile_out_col(J, T, j);
-    }
-    for (int i = threadIdx.x; i < BK; i += 256) {
-        ak_lo[i] = i < kc ? deposit(i, J.a_k, 0, kc_log) : 0;
-        bk_lo[i] = i < kc ? deposit(i, J.b_k, 0, kc_log) : 0;
-    }
     chunk_steps(J.a_k, kc_log, k_log, a_step);
     chunk_steps(J.b_k, kc_log, k_log, b_step);
+    tile_tables<BM, BN, BK, 256>(J, T, kc_log, row_a, row_c, col_b, col_c, ak_lo, bk_lo);
     __syncthreads();
     const TN_GLOBAL double2* __restrict__ A = gload<double2>(J.A);
     const TN_GLOBAL double2* __restrict__ B = gload<double2>(J.B);
