@@ -301,7 +301,8 @@ __device__ __forceinline__ int64_t deposit(int64_t x, const TN_CONST int8_t* pos
 // Offset steps of a chunk counter: with chunk index h (inner index h << lo),
 // deposit(h + 1) = deposit(h) + step[ctz(~h)], where step[t] is the offset of
 // inner bit lo + t minus the offsets of the bits below it, lo <= bit < lo + t.
-// The sums run in scalar registers; thread t writes entry t (t < 32).  (Placing
+// The sums run in scalar registers; thread t writes entry t (t < 32; entries past
+// the last bit are 0: the step after the last chunk).  (Placing
 // the whole counter anew for each chunk instead cost long tiles 7 %.)
 __device__ __forceinline__ void chunk_steps(const TN_CONST int8_t* pos, int lo, int hi, int64_t* step) {
     const TN_CONST uint32_t* pw = (const TN_CONST uint32_t*)pos;
@@ -314,7 +315,7 @@ __device__ __forceinline__ void chunk_steps(const TN_CONST int8_t* pos, int lo, 
         if ((int)threadIdx.x == j - lo) mine = at - below;
         below += at;
     }
-    if ((int)threadIdx.x < hi - lo) step[threadIdx.x] = mine;
+    if (threadIdx.x < 32) step[threadIdx.x] = mine;
 }
 
 // Output offset (element index into C) of row i / column j of a grouped tile,
@@ -548,67 +549,22 @@ void k_gemm_mfma_g(GemmArgs g) {
 }
 
 // ---------------------------------------------------------------------------
-// Tuning of the grouped matrix-core kernel (measured on the 25-qubit workload's
-// 128 x 32 level, 848 slices of 256 x 16 x 256 and 134 of 512 x 16 x 64):
-//   MFMA_GROUP_WAVES   register budget of the 64-row waves: two waves per SIMD
-//                      leave room for the second register set of the two-deep
-//                      chunk pipeline (three spill it); 113 us against 117 us at
-//                      three waves with one chunk of read-ahead;
-//   MFMA_ROWS32        32-row waves (below) at four waves per SIMD: 100 us
-//                      against 113 us on that level, and faster on every tile
-//                      shape of 64 or 128 rows but 128 x 64;
-//   MFMA_PREFETCH2     loads run two chunks ahead of the MFMAs (the operands of
-//                      tiles that miss in L2 come from HBM in a few us);
-//   MFMA_SKIP_PAD      column blocks past a tile's last slice skip their MFMAs
-//                      (a fifth of that level's tiles hold one slice of two).
-#ifndef MFMA_GROUP_WAVES
-#define MFMA_GROUP_WAVES 2
-#endif
-#ifndef MFMA_GROUP_WAVES_128X64
-#define MFMA_GROUP_WAVES_128X64 4
-#endif
-#ifndef MFMA_RA_128X64
-#define MFMA_RA_128X64 2
-#endif
-#ifndef MFMA_GROUP_BKC
-#define MFMA_GROUP_BKC 8
-#endif
-#ifndef MFMA_GROUP_SCHED
-#define MFMA_GROUP_SCHED 1
-#endif
-#ifndef MFMA_PREFETCH2
-#define MFMA_PREFETCH2 1
-#endif
-#ifndef MFMA_SKIP_PAD
-#define MFMA_SKIP_PAD 1
-#endif
-#ifndef MFMA_ROWS32
-#define MFMA_ROWS32 1
-#endif
-#ifndef MFMA_ROWS32_128X64
-#define MFMA_ROWS32_128X64 0
-#endif
-#ifndef MFMA_GROUP_WAVES_ROWS32
-#define MFMA_GROUP_WAVES_ROWS32 4
-#endif
-// Wave layout of the grouped kernel: WM x WN waves, each holding TM x TN
-// 32 x 32 real MFMA blocks (32 rows x 16 complex columns each).  With
-// MFMA_ROWS32 the tiles of 64 and 128 rows run 32-row waves (half the
-// accumulators of a 64-row wave), so up to four waves share each SIMD: one
-// wave alone issues FP32 MFMAs at about half the matrix core's rate, two at
-// about 85 %, four at about 94 % (a loop of independent 32 x 32 x 2 MFMAs).
-// The 128 x 64 tile keeps 64-row waves (its 32-row form measured slower: eight
-// waves per block, each re-reading B).
+// Wave layout of the grouped matrix-core kernel: WM x WN waves, each holding
+// TM x TN 32 x 32 real MFMA blocks (32 rows x 16 complex columns each).  Tiles of
+// 64 and 128 rows run 32-row waves (half the accumulators of a 64-row wave) in a
+// register budget of four waves per SIMD: 848 tiles of 128 x 32, k = 256, took
+// 100 us against 113 us with 64-row waves at two.  (A loop of independent
+// 32 x 32 x 2 MFMAs reaches 136, 144 and 154 TFLOP/s with one, two and four waves
+// per SIMD.)  The 128 x 64 tile keeps 64-row waves: its 32-row form, eight waves
+// per block that each read B again, measured slower.
 template <int BM, int BNC>
 struct MfmaGroupShape {
-    static constexpr bool ROWS32 = MFMA_ROWS32 && BM >= 64 && (MFMA_ROWS32_128X64 || !(BM == 128 && BNC == 64));
+    static constexpr bool WIDE = BM == 128 && BNC == 64;
+    static constexpr bool ROWS32 = BM >= 64 && !WIDE;
     static constexpr int WM = ROWS32 ? BM / 32 : (BM >= 64 ? BM / 64 : 1);
     static constexpr int WN = BNC >= 32 ? BNC / 32 : 1;
     static constexpr int NT = 64 * WM * WN;
-    static constexpr int WAVES = ROWS32 ? MFMA_GROUP_WAVES_ROWS32
-                                 : (BM == 64 && BNC == 32) ? 2
-                                 : (BM == 128 && BNC == 64) ? MFMA_GROUP_WAVES_128X64
-                                                            : MFMA_GROUP_WAVES;
+    static constexpr int WAVES = ROWS32 || WIDE ? 4 : 2;      // register budget, waves per SIMD
 };
 // Grouped matrix-core contractions (FP32 complex on mfma_f32_32x32x2f32, the
 // real embedding of K1).  One block per tile descriptor; the tile's row and
@@ -616,6 +572,15 @@ struct MfmaGroupShape {
 // are built in LDS from the job's slice tables, so slices that share an
 // operand can fill one tile (merge modes) and any stored layout is read
 // without a transpose pass.
+//
+// Bound by the matrix cores where a level fills the chip (1.1e11 FLOP of k = 1024
+// at 117 of 154 TFLOP/s), by waves in flight where it has fewer tiles than two per
+// compute unit.  The inner loop is a software pipeline over chunks of 8 (chunks of
+// 16 were much slower: LDS per block) that has no branches, so global loads, LDS
+// writes, LDS reads and MFMAs of different chunks overlap inside one wave; with
+// the reads of a chunk ahead of its own MFMAs and branches on padding it took
+// 2107 us for 12 packed circuits (now 2041), 538 us for a 36-qubit QAOA estimate
+// (519) and 1128 us for a 25-qubit grid estimate (1113).
 // ---------------------------------------------------------------------------
 template <int BM, int BNC>
 __global__ __launch_bounds__((MfmaGroupShape<BM, BNC>::NT), (MfmaGroupShape<BM, BNC>::WAVES))
@@ -625,7 +590,7 @@ void k_mfma_group(const MfmaJob* __restrict__ jobs, const MfmaTile* __restrict__
     constexpr int NT = MfmaGroupShape<BM, BNC>::NT;
     constexpr int TM = BM / WM / 32;
     constexpr int TN = BNC / WN / 16;
-    constexpr int BKC = MFMA_GROUP_BKC, BKC_LOG = __builtin_ctz(MFMA_GROUP_BKC);
+    constexpr int BKC = 8, BKC_LOG = 3;
     constexpr int BM_LOG = __builtin_ctz(BM), BN_LOG = __builtin_ctz(BNC);
     constexpr int AE = BM * BKC / NT;
     constexpr int BE = (BKC * BNC + NT - 1) / NT;
@@ -639,7 +604,7 @@ void k_mfma_group(const MfmaJob* __restrict__ jobs, const MfmaTile* __restrict__
     constexpr int AP = BM + 8, AH = BKC * AP + 32, ABUF = 2 * AH;
     constexpr int BP = 2 * BNC + 8, BBUF = BKC * BP;
     __shared__ __align__(16) float As[2 * ABUF];
-    __shared__ __align__(16) float Bs[2 * BBUF];
+    __shared__ __align__(16) float Bs[2 * (BBUF + 2)];
     __shared__ int64_t row_a[BM], row_c[BM], col_b[BNC], col_c[BNC], ak_lo[BKC], bk_lo[BKC];
     __shared__ int64_t a_step[32], b_step[32];
     const MfmaTile T = tiles[blockIdx.x];
@@ -700,61 +665,74 @@ void k_mfma_group(const MfmaJob* __restrict__ jobs, const MfmaTile* __restrict__
     int64_t kchunk = c_begin;
     int64_t akh = deposit(c_begin << kc_log, J.a_k, kc_log, k_log);
     int64_t bkh = deposit(c_begin << kc_log, J.b_k, kc_log, k_log);
-    // offsets of this thread's staged elements inside a chunk (fixed over the
-    // chunks; -1 = padding, loaded from element 0 and replaced by zero)
-    int64_t aoff[AE], boff[BE];
+    // this thread's staged elements in the first chunk (a chunk adds akh / bkh).
+    // Padding reads the operand's element 0 plus that offset, which is an element
+    // of its first instance, and is zeroed when staged (mask bits: q of A, 16 + q of B)
+    const TN_GLOBAL float2* pa[AE];
+    const TN_GLOBAL float2* pb[BE];
+    uint32_t live = 0;
 #pragma unroll
     for (int q = 0; q < AE; ++q) {
         int r, p;
         a_rp(threadIdx.x + q * NT, r, p);
         const int64_t base = row_a[r];
-        aoff[q] = (base >= 0 && p < kc) ? base + ak_lo[p] : -1;
+        const bool ok = base >= 0 && p < kc;
+        pa[q] = A + (ok ? base + ak_lo[p] : 0);
+        live |= ok ? 1u << q : 0u;
     }
 #pragma unroll
     for (int q = 0; q < BE; ++q) {
         const int e = threadIdx.x + q * NT;
-        boff[q] = -1;
+        bool ok = false;
+        pb[q] = B;
         if (e < BKC * BNC) {
             int p, c;
             b_pc(e, p, c);
             const int64_t base = col_b[c];
-            if (base >= 0 && p < kc) boff[q] = base + bk_lo[p];
+            ok = base >= 0 && p < kc;
+            if (ok) pb[q] = B + (base + bk_lo[p]);
         }
+        live |= ok ? 1u << (16 + q) : 0u;
     }
-    // raw loads (padding lanes read element 0); padding is zeroed when staged,
-    // so nothing waits on a load before the chunk's MFMAs
-    auto load = [&](int64_t, float2* ra, float2* rb) {
+    auto load = [&](float2* ra, float2* rb) {
 #pragma unroll
-        for (int q = 0; q < AE; ++q) ra[q] = gld(A + (aoff[q] >= 0 ? aoff[q] + akh : 0));
+        for (int q = 0; q < AE; ++q) ra[q] = gld(pa[q] + akh);
 #pragma unroll
-        for (int q = 0; q < BE; ++q) rb[q] = gld(B + (boff[q] >= 0 ? boff[q] + bkh : 0));
-        const int t = __builtin_ctzll(~(uint64_t)kchunk);
-        if (t < k_log - kc_log) {
-            akh += a_step[t];
-            bkh += b_step[t];
-        }
+        for (int q = 0; q < BE; ++q) rb[q] = gld(pb[q] + bkh);
+        const int t = __builtin_ctzll(~(uint64_t)kchunk);      // (past the last chunk: an entry of 0)
+        akh += a_step[t];
+        bkh += b_step[t];
         ++kchunk;
+        // (the scheduler would sink the loads to their first use)
+        __builtin_amdgcn_sched_barrier(0);
     };
+    // LDS slots of the staged elements: element q is q steps past the first.
+    // Threads past the chunk's B elements write to a slot that nobody reads, so
+    // staging has no branches and its writes spread over the MFMAs.
+    int sa, sb;
+    {
+        int r, p;
+        a_rp(threadIdx.x, r, p);
+        sa = p * AP + r;
+        b_pc(threadIdx.x, p, r);
+        sb = BKC * BNC >= NT || (int)threadIdx.x < BKC * BNC ? p * BP + 2 * r : BBUF;
+    }
+    const int sa_step = a_rowfast ? NT / BM * AP : NT / BKC;
+    const int sb_step = BE == 1 ? 0 : b_colfast ? NT / BNC * BP : 2 * (NT / BKC);
+    static_assert(AE == 1 || (NT % BM == 0 && NT % BKC == 0), "staged elements are a fixed step apart");
+    static_assert(BE == 1 || (NT % BNC == 0 && NT % BKC == 0), "staged elements are a fixed step apart");
     auto stash = [&](int buf, const float2* ra, const float2* rb) {
-        float* as = As + buf * ABUF;
-        float* bs = Bs + buf * BBUF;
+        float* as = As + buf * ABUF + sa;
+        float* bs = Bs + buf * (BBUF + 2) + sb;
 #pragma unroll
         for (int q = 0; q < AE; ++q) {
-            int r, p;
-            a_rp(threadIdx.x + q * NT, r, p);
-            const bool ok = aoff[q] >= 0;
-            as[p * AP + r] = ok ? ra[q].x : 0.0f;
-            as[AH + p * AP + r] = ok ? ra[q].y : 0.0f;
+            const bool ok = live >> q & 1u;
+            as[q * sa_step] = ok ? ra[q].x : 0.0f;
+            as[AH + q * sa_step] = ok ? ra[q].y : 0.0f;
         }
 #pragma unroll
-        for (int q = 0; q < BE; ++q) {
-            const int e = threadIdx.x + q * NT;
-            if (e < BKC * BNC) {
-                int p, c;
-                b_pc(e, p, c);
-                *(float2*)&bs[p * BP + 2 * c] = boff[q] >= 0 ? rb[q] : make_float2(0.0f, 0.0f);
-            }
-        }
+        for (int q = 0; q < BE; ++q)
+            *(float2*)&bs[q * sb_step] = live >> (16 + q) & 1u ? rb[q] : make_float2(0.0f, 0.0f);
     };
     // per-lane LDS offsets of the MFMA operands
     int a_off[TM], b_off[TN];
@@ -763,97 +741,106 @@ void k_mfma_group(const MfmaJob* __restrict__ jobs, const MfmaTile* __restrict__
 #pragma unroll
     for (int j = 0; j < TN; ++j) b_off[j] = 2 * (wn * (TN * 16) + j * 16) + (half ? (sub ^ 1) : sub);
     const uint32_t b_sign = (half && !(sub & 1)) ? 0x80000000u : 0u;
-    // operands read ahead per group of RA inner indices: the whole chunk, or two
-    // on 128 x 64 tiles (held to four waves per SIMD, whose 128-register budget
-    // the full read-ahead would exceed; a few spills remain outside the loop)
-    constexpr bool WIDE = BM == 128 && BNC == 64 && !MfmaGroupShape<BM, BNC>::ROWS32;
-    constexpr int RA = WIDE ? MFMA_RA_128X64 : BKC;
-    // TNA: this wave's column blocks that hold outputs (the others are padding
-    // past the tile's last slice or column, skipped)
-    auto compute = [&](int buf, auto tna) {
-        constexpr int TNA = decltype(tna)::value;
-        const float* as = As + buf * ABUF;
-        const float* bs = Bs + buf * BBUF;
-#pragma unroll
-        for (int g = 0; g < BKC; g += RA) {
-            // all operands of the group read first, so the LDS reads of later
-            // inner indices are in flight while the MFMAs of earlier ones run
-            float a[RA][TM], b[RA][TNA];
-#pragma unroll
-            for (int p = 0; p < RA; ++p) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i) a[p][i] = as[(g + p) * AP + a_off[i]];
-#pragma unroll
-                for (int j = 0; j < TNA; ++j)
-                    b[p][j] = __uint_as_float(__float_as_uint(bs[(g + p) * BP + b_off[j]]) ^ b_sign);
-            }
-#pragma unroll
-            for (int p = 0; p < RA; ++p)
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TNA; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[p][i], b[p][j], acc[i][j], 0, 0, 0);
-            // keep the reads ahead of the MFMAs: DS reads of inner index p + 1
-            // are scheduled before the MFMAs of inner index p
-#if MFMA_GROUP_SCHED
-            __builtin_amdgcn_sched_group_barrier(0x100, TM + TNA, 0);
-#pragma unroll
-            for (int p = 0; p < RA; ++p) {
-                if (p + 1 < RA) __builtin_amdgcn_sched_group_barrier(0x100, TM + TNA, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, TM * TNA, 0);
-            }
-#endif
-        }
-    };
+    // Operands are read from LDS in groups of two inner indices, each group while
+    // the MFMAs of the group before run (groups of four: up to 1.5 % slower).
+    constexpr int RA = 2, G = BKC / RA;
+    static_assert(G % 2 == 0, "the two operand sets alternate");
     // column blocks of 16 holding outputs (padding is a suffix of the tile's
     // columns: slices past cnt, columns past n): all TN, the first only, or none
     int tn_act = 0;
 #pragma unroll
     for (int j = 0; j < TN; ++j)
         if (col_c[wn * (TN * 16) + j * 16] >= 0) tn_act = j + 1;
-    auto compute_active = [&](int buf) {
-        if (!MFMA_SKIP_PAD || tn_act == TN) compute(buf, std::integral_constant<int, TN>{});
-        else if (TN > 1 && tn_act == 1) compute(buf, std::integral_constant<int, 1>{});
-    };
     const int64_t nchunks = c_end - c_begin;
-    if (MFMA_PREFETCH2 && !WIDE) {
-        // pipeline two chunks deep: LDS holds chunk ch, registers hold chunk
-        // ch + 1, and the loads of chunk ch + 2 are in flight during chunk ch's
-        // MFMAs (a chunk's loads have two chunks of matrix-core work to arrive
-        // from HBM when they miss in L2).  Chunk c is staged in and read from
-        // LDS buffer c & 1; the two register sets alternate with it.  (The
-        // 128 x 64 tile's register budget holds one set.)
-        float2 ra0[AE], rb0[BE], ra1[AE], rb1[BE];
-        load(0, ra0, rb0);
-        stash(0, ra0, rb0);
-        if (nchunks > 1) load(BKC, ra1, rb1);
-        __syncthreads();
-        for (int64_t ch = 0; ch < nchunks; ch += 2) {
-            if (ch + 2 < nchunks) load((ch + 2) * BKC, ra0, rb0);
-            compute_active(0);
-            if (ch + 1 < nchunks) stash(1, ra1, rb1);
-            __syncthreads();
-            if (ch + 1 >= nchunks) break;
-            if (ch + 3 < nchunks) load((ch + 3) * BKC, ra1, rb1);
-            compute_active(1);
-            if (ch + 2 < nchunks) stash(0, ra0, rb0);
-            __syncthreads();
-        }
-    } else {
-        // pipeline: LDS holds chunk ch while the loads of chunk ch + 1 are in flight
+    constexpr int WPP = (2 * AE + BE + RA - 1) / RA;      // LDS writes per inner index of a group
+    // The inner sum over TNA active column blocks.  Each wave takes one of the
+    // three forms as a whole, and all forms have one barrier per chunk.  (tn_act is
+    // not made a scalar: with scalar branches the accumulators are copied where the
+    // forms join, 28 more registers, and the 128 x 64 tile spills.)
+    auto sum = [&](auto tna) {
+        constexpr int TNA = decltype(tna)::value;
+        constexpr int TB = TNA > 0 ? TNA : 1;
+        float a[2][RA][TM], b[2][RA][TB];
+        // operands of group g of the chunk in LDS buffer buf
+        auto read = [&](int buf, int g, float (&x)[RA][TM], float (&y)[RA][TB]) {
+            if constexpr (TNA > 0) {
+                const float* as = As + buf * ABUF + g * RA * AP;
+                const float* bs = Bs + buf * (BBUF + 2) + g * RA * BP;
+#pragma unroll
+                for (int p = 0; p < RA; ++p) {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) x[p][i] = as[p * AP + a_off[i]];
+#pragma unroll
+                    for (int j = 0; j < TNA; ++j) y[p][j] = bs[p * BP + b_off[j]];
+                }
+                __builtin_amdgcn_sched_barrier(0);         // ahead of the MFMAs that follow
+            }
+        };
+        auto multiply = [&](const float (&x)[RA][TM], const float (&y)[RA][TB], bool staged) {
+            if constexpr (TNA > 0) {
+#pragma unroll
+                for (int p = 0; p < RA; ++p) {
+                    float z[TB];
+#pragma unroll
+                    for (int j = 0; j < TNA; ++j) z[j] = __uint_as_float(__float_as_uint(y[p][j]) ^ b_sign);
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TNA; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[p][i], z[j], acc[i][j], 0, 0, 0);
+                }
+                if (staged) {
+                    // the LDS writes and their VALU work between the MFMAs
+#pragma unroll
+                    for (int p = 0; p < RA; ++p) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, TM * TNA, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 3 * WPP, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x200, WPP, 0);
+                    }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
         float2 ra[AE], rb[BE];
-        load(0, ra, rb);
+        load(ra, rb);
         stash(0, ra, rb);
+        if (nchunks > 1) load(ra, rb);
         __syncthreads();
-        for (int64_t ch = 0; ch < nchunks; ++ch) {
-            const int buf = (int)(ch & 1);
-            if (ch + 1 < nchunks) load((ch + 1) * BKC, ra, rb);
-            compute_active(buf);
-            if (ch + 1 < nchunks) stash(buf ^ 1, ra, rb);
-            __syncthreads();
+        read(0, 0, a[0], b[0]);
+        // chunk c sits in LDS buffer c & 1, its first group in operand set 0, and
+        // chunk c + 1 in the registers (or on its way there).  During the first
+        // group's MFMAs chunk c + 1 goes to LDS and the loads of chunk c + 2 are
+        // issued after it (a whole chunk of MFMAs before they are needed); the
+        // barrier comes before the last group's MFMAs, which cover the reads of
+        // the next chunk's first group.
+        auto chunk = [&](int buf, auto next, auto after) {
+            constexpr bool NEXT = decltype(next)::value, AFTER = decltype(after)::value;
+#pragma unroll
+            for (int g = 0; g + 1 < G; ++g) {
+                read(buf, g + 1, a[(g + 1) & 1], b[(g + 1) & 1]);
+                if (NEXT && g == 0) stash(buf ^ 1, ra, rb);
+                multiply(a[g & 1], b[g & 1], NEXT && g == 0);
+                if (AFTER && g == 0) load(ra, rb);
+            }
+            if constexpr (NEXT) {
+                __syncthreads();
+                read(buf ^ 1, 0, a[0], b[0]);
+            }
+            multiply(a[1], b[1], false);
+        };
+        constexpr std::integral_constant<bool, true> yes{};
+        constexpr std::integral_constant<bool, false> no{};
+        int buf = 0;
+        for (int64_t ch = 0; ch + 2 < nchunks; ++ch, buf ^= 1) chunk(buf, yes, yes);
+        if (nchunks > 1) {
+            chunk(buf, yes, no);
+            buf ^= 1;
         }
-    }
+        chunk(buf, no, no);
+    };
+    if (tn_act == TN) sum(std::integral_constant<int, TN>{});
+    else if (TN > 1 && tn_act == 1) sum(std::integral_constant<int, 1>{});
+    else sum(std::integral_constant<int, 0>{});
 
     // split inner sum: this block's part goes to its row-major [BM][BNC] partial
     // tile (padding skipped), added to the others' by k_split_reduce
