@@ -262,10 +262,12 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // ---------------------------------------------------------------------------
 // The whole network of a block of 16 RT rows in one launch: normalized rows
 // and activations stay in LDS, eight waves take 16 CT output columns each, and
-// the products run on the FP32 matrix cores (v_mfma_f32_16x16x4f32).  A lane
-// takes four consecutive inner indices of its row (LDS) and of its weight row
-// (global, one 16-byte load), so instruction j of a group of 16 inner indices
-// multiplies indices kb + 4 (lane / 16) + j.
+// the products run on the FP32 matrix cores (v_mfma_f32_16x16x4f32, which adds
+// its four products one after another like a chain of fmaf).  Every sum runs over
+// ascending inner indices, as in the kernels of one layer each, so both routes
+// give the same bits: instruction q of a group of 16 takes indices 4 q + lane / 16.
+// In LDS the 16 are stored 4 x 4 transposed, so a lane reads its four with one
+// 16-byte load; weights are transposed in registers (four lane swaps).
 //   TRAIN = false: the output column only, layers in place in one LDS buffer.
 //   TRAIN = true: also the loss partial of the block, dL/dy, and the gradients
 //     through the layers (the same products against W instead of W^T), each
@@ -285,10 +287,36 @@ struct MlpArgs {
     int n_in, width, depth, pitch;
 };
 
+// LDS position of column c of a row: 4 x 4 transposed within its group of 16
+__device__ __forceinline__ int lds_col(int c) { return (c & ~15) | (c & 3) << 2 | (c >> 2 & 3); }
+
+// lane group g's element q becomes lane group q's element g (groups of 16 lanes)
+__device__ __forceinline__ v4f transpose_groups(v4f x) {
+    typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+    uint32_t u[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) u[q] = __float_as_uint(x[q]);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const v2u t = __builtin_amdgcn_permlane32_swap(u[q], u[q + 2], false, false);
+        u[q] = t[0];
+        u[q + 2] = t[1];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q += 2) {
+        const v2u t = __builtin_amdgcn_permlane16_swap(u[q], u[q + 1], false, false);
+        u[q] = t[0];
+        u[q + 1] = t[1];
+    }
+    return v4f{__uint_as_float(u[0]), __uint_as_float(u[1]), __uint_as_float(u[2]), __uint_as_float(u[3])};
+}
+
+// (128 registers where two blocks share a CU: four waves per SIMD)
 template <int RT, int CT, bool TRAIN>
-__global__ __launch_bounds__(512) void k_mlp_fused(MlpArgs a) {
+__global__ __launch_bounds__(512, CT == 1 && !TRAIN ? 4 : 2) void k_mlp_fused(MlpArgs a) {
     constexpr int R = 16 * RT;
     extern __shared__ __align__(16) float lds[];
+    __shared__ __align__(16) float wo[256];
     __shared__ float dys[R];
     __shared__ double ls[R];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -298,134 +326,178 @@ __global__ __launch_bounds__(512) void k_mlp_fused(MlpArgs a) {
     const int64_t bufsz = (int64_t)R * pitch;
     const int64_t lsz = (int64_t)W * W + W;                  // parameters of a hidden layer past the first
     const float* p1 = a.params + (int64_t)D * W + W;         // second layer
-    // rows in, normalized; inner columns up to a multiple of 16 are zero
-    const int din16 = (D + 15) & ~15, w16 = (W + 15) & ~15;
-    for (int e = tid; e < R * din16; e += 512) {
-        const int r = e / din16, c = e - r * din16;
-        float v = 0.0f;
-        if (c < D && r0 + r < a.n) {
-            v = (a.x[(r0 + r) * D + c] - a.mean[c]) * a.istd[c];
-            if (TRAIN) a.xn[(r0 + r) * D + c] = v;
-        }
-        lds[r * pitch + c] = v;
-    }
-    __syncthreads();
     const int c0 = wave * 16 * CT;                           // this wave's first column
-    v4f acc[RT][CT];
-    // acc = In Wt^T (bwd = false: Wt is W x K, lane's column is a row of it) or
-    // In Wt (bwd = true: Wt is K x W), K <= 256 inner indices in groups of 16
-    auto product = [&](const float* in, const float* Wt, int K, auto bwd) {
+    constexpr int G = 8;                                     // groups of 16 inner indices in registers
+    v4f acc[RT][CT], w[CT][G], wt[CT];
+    float bias[CT];
+    // w = the whole inner groups g0 .. g0 + G of a layer's weights, wt = the ragged
+    // group behind its last whole one (bwd = false: Wt is W x K, the lane's column is
+    // a row of it; true: Wt is K x W).  Columns past W repeat the last one: their
+    // results are not used.  The code is kept short: a block runs each part of the
+    // kernel once or twice, so it waits for instructions as much as for data.
+    auto weights = [&](const float* Wt, int K, int g0, auto bwd) {
         constexpr bool BWD = decltype(bwd)::value;
-        constexpr int G = 8;                                 // groups whose weights are loaded ahead
+        const int nf = K >> 4;
+        uint32_t at[CT];
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            const int c = c0 + 16 * j + sub, col = c < W ? c : W - 1;
+            at[j] = BWD ? grp * W + col : col * K + 4 * grp;
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (g0 + g >= nf) break;
+            const float* p = Wt + 16 * (g0 + g) * (BWD ? W : 1);
+#pragma unroll
+            for (int j = 0; j < CT; ++j)
+                if constexpr (BWD) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) w[j][g][q] = (p + 4 * q * W)[at[j]];
+                } else {
+                    w[j][g] = *(const v4f_u*)(p + at[j]);
+                }
+        }
+        if ((K & 15) && nf <= g0 + G) {
+            const float* p = Wt + 16 * nf * (BWD ? W : 1);
+#pragma unroll
+            for (int j = 0; j < CT; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    wt[j][q] = 0.0f;
+                    if (16 * nf + 4 * q + grp < K) wt[j][q] = p[at[j] + (BWD ? 4 * q * W : 4 * q - 3 * grp)];
+                }
+        }
+    };
+    // acc = In Wt^T or In Wt, K <= 256 inner indices; w and wt hold the first groups
+    auto product = [&](const float* in, const float* Wt, int K, auto bwd) {
 #pragma unroll
         for (int i = 0; i < RT; ++i)
 #pragma unroll
             for (int j = 0; j < CT; ++j) acc[i][j] = v4f{0, 0, 0, 0};
-        const int ng = (K + 15) >> 4;
-        for (int g0 = 0; g0 < ng; g0 += G) {
-            v4f w[CT][G];
+        const int nf = K >> 4;
+        auto group = [&](int at, const v4f* wg, int step) {
+            v4f x[RT];
 #pragma unroll
-            for (int j = 0; j < CT; ++j) {
-                const int col = c0 + 16 * j + sub;
+            for (int i = 0; i < RT; ++i) x[i] = *(const v4f*)&in[(16 * i + sub) * pitch + 16 * at + 4 * grp];
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const int k = 16 * (g0 + g) + 4 * grp;
-                    w[j][g] = v4f{0, 0, 0, 0};
-                    if (col >= W || k >= K) continue;
-                    if constexpr (BWD) {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            if (k + q < K) w[j][g][q] = Wt[(int64_t)(k + q) * W + col];
-                    } else {
-                        const float* p = Wt + (int64_t)col * K + k;
-                        if (k + 3 < K) {
-                            w[j][g] = *(const v4f_u*)p;
-                        } else {
-#pragma unroll
-                            for (int q = 0; q < 3; ++q)
-                                if (k + q < K) w[j][g][q] = p[q];
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                if (g0 + g >= ng) break;
-                v4f x[RT];
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
                 for (int i = 0; i < RT; ++i)
-                    x[i] = *(const v4f*)&in[(16 * i + sub) * pitch + 16 * (g0 + g) + 4 * grp];
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
+                    for (int j = 0; j < CT; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i][q], wg[j * step][q], acc[i][j], 0, 0, 0);
+        };
+        for (int g0 = 0; g0 < nf || g0 == 0; g0 += G) {
+            if (g0 > 0) weights(Wt, K, g0, bwd);
 #pragma unroll
-                    for (int i = 0; i < RT; ++i)
+            for (int g = 0; g < G; ++g) {
+                if (g0 + g >= nf) break;
+                if constexpr (!decltype(bwd)::value) {
 #pragma unroll
-                        for (int j = 0; j < CT; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i][q], w[j][g][q], acc[i][j], 0, 0, 0);
+                    for (int j = 0; j < CT; ++j) w[j][g] = transpose_groups(w[j][g]);
+                }
+                group(g0 + g, &w[0][g], G);
             }
         }
+        if (K & 15) group(nf, wt, 1);
     };
+    constexpr std::integral_constant<bool, false> fwd{};
+    constexpr std::integral_constant<bool, true> back{};
+    // a layer's biases and weights, the biases first (loads arrive in order)
+    auto layer = [&](const float* Wl, int K) {
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            const int col = c0 + 16 * j + sub;
+            bias[j] = Wl[(int64_t)K * W + (col < W ? col : W - 1)];
+        }
+        weights(Wl, K, 0, fwd);
+    };
+    // rows of an LDS buffer to global memory, a wave a row
+    auto save = [&](const float* from, float* to, int cols) {
+        for (int r = wave; r < R && r0 + r < a.n; r += 8)
+            for (int c = lane; c < cols; c += 64) to[(r0 + r) * cols + c] = from[r * pitch + lds_col(c)];
+    };
+    const int din16 = (D + 15) & ~15, w16 = (W + 15) & ~15;
+    const float* Wo = p1 + (int64_t)(a.depth - 1) * lsz;     // output layer
+    const int orl = 16 * wave + 4 * grp + sub;               // this thread's row there, if it has one
+    const bool orv = wave < RT && sub < 4;
+    const int64_t orow = r0 + orl;
+    float tr = 0.0f, wr = 1.0f;
+    if (TRAIN && orv && orow < a.n) {
+        tr = a.t[orow];
+        if (a.w) wr = a.w[orow];
+    }
+    if (tid < 256) wo[lds_col(tid)] = tid < W ? Wo[tid] : 0.0f;
+    const float bo = Wo[W];
+    if (c0 < w16) layer(a.params, D);
+    // rows in, normalized; inner columns up to a multiple of 16 are zero
+    for (int c = lane; c < din16; c += 64) {
+        const float m = c < D ? a.mean[c] : 0.0f, is = c < D ? a.istd[c] : 0.0f;
+        for (int r = wave; r < R; r += 8)
+            lds[r * pitch + lds_col(c)] = c < D && r0 + r < a.n ? (a.x[(r0 + r) * D + c] - m) * is : 0.0f;
+    }
+    __syncthreads();
+    if (TRAIN) save(lds, a.xn, D);
     // element e of a lane's result is row 4 grp + e of its block
     float* cur = lds;
     for (int l = 0; l < a.depth; ++l) {
         const float* Wl = l == 0 ? a.params : p1 + (l - 1) * lsz;
-        const int K = l == 0 ? D : W;
-        const float* bl = Wl + (int64_t)K * W;
-        if (c0 < w16) product(cur, Wl, K, std::integral_constant<bool, false>{});
         float* nxt = TRAIN ? cur + bufsz : cur;
+        float bl[CT];
+        if (c0 < w16) {
+            product(cur, Wl, l == 0 ? D : W, fwd);
+#pragma unroll
+            for (int j = 0; j < CT; ++j) bl[j] = bias[j];
+            // the next product's weights arrive during this layer's end
+            if (l + 1 < a.depth) layer(p1 + l * lsz, W);
+            else if (TRAIN && l > 0) weights(p1 + (l - 1) * lsz, W, 0, back);
+        }
         if (!TRAIN) __syncthreads();                         // every wave has read the rows it overwrites
         if (c0 < w16) {
 #pragma unroll
             for (int j = 0; j < CT; ++j) {
-                const int col = c0 + 16 * j + sub;
+                const int col = c0 + 16 * j + sub, pos = lds_col(col);
                 if (col >= w16) continue;
-                const float bias = col < W ? bl[col] : 0.0f;
 #pragma unroll
                 for (int i = 0; i < RT; ++i)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const int r = 16 * i + 4 * grp + e;
-                        const float s = acc[i][j][e] + bias;
-                        const float v = col < W && s > 0.0f ? s : 0.0f;
-                        nxt[r * pitch + col] = v;
-                        if (TRAIN && col < W && r0 + r < a.n)
-                            a.acts[((int64_t)l * a.n + r0 + r) * W + col] = v;
+                        const float s = acc[i][j][e] + bl[j];
+                        nxt[(16 * i + 4 * grp + e) * pitch + pos] = col < W && s > 0.0f ? s : 0.0f;
                     }
             }
         }
         cur = nxt;
         __syncthreads();
     }
-    // output layer: 512 / R threads per row, fixed-order butterfly
-    const float* Wo = p1 + (int64_t)(a.depth - 1) * lsz;
-    constexpr int T = 512 / R;
-    {
-        const int r = tid / T, q = tid % T;
-        float s = 0.0f;
-        for (int c = q; c < W; c += T) s = fmaf(cur[r * pitch + c], Wo[c], s);
+    // output layer: a wave per 16 rows (all 16 columns of the product are the one)
+    if (wave < RT) {
+        v4f o = v4f{0, 0, 0, 0};
+        for (int g = 0; g < w16; g += 16) {
+            const v4f x = *(const v4f*)&cur[(16 * wave + sub) * pitch + g + 4 * grp], y = *(const v4f*)&wo[g + 4 * grp];
 #pragma unroll
-        for (int off = T / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
-        const float y = s + Wo[W];
-        if (q == 0) {
-            const int64_t row = r0 + r;
+            for (int q = 0; q < 4; ++q) o = __builtin_amdgcn_mfma_f32_16x16x4f32(x[q], y[q], o, 0, 0, 0);
+        }
+        const float y = (sub == 0 ? o[0] : sub == 1 ? o[1] : sub == 2 ? o[2] : o[3]) + bo;
+        if (orv) {
             if (!TRAIN) {
-                if (row < a.n) a.y[row] = y;
+                if (orow < a.n) a.y[orow] = y;
             } else {
                 float dy = 0.0f;
                 double l = 0.0;
-                if (row < a.n) {
-                    const float wi = a.w ? a.w[row] : 1.0f;
-                    const float d = y - a.t[row];
-                    dy = 2.0f * wi * d / (float)a.n;
-                    l = (double)wi * (double)d * (double)d;
-                    a.dy[row] = dy;
+                if (orow < a.n) {
+                    const float d = y - tr;
+                    dy = 2.0f * wr * d / (float)a.n;
+                    l = (double)wr * (double)d * (double)d;
+                    a.dy[orow] = dy;
                 }
-                dys[r] = dy;
-                ls[r] = l;
+                dys[orl] = dy;
+                ls[orl] = l;
             }
         }
     }
     if constexpr (TRAIN) {
+        for (int l = 0; l < a.depth; ++l) save(lds + (l + 1) * bufsz, a.acts + (int64_t)l * a.n * W, W);
         __syncthreads();
         if (tid == 0) {
             double l = 0.0;
@@ -433,77 +505,86 @@ __global__ __launch_bounds__(512) void k_mlp_fused(MlpArgs a) {
             a.part[blockIdx.x] = l;
         }
         // gradient of the last hidden layer's pre-activations, over its activations
-        for (int e = tid; e < R * w16; e += 512) {
-            const int r = e / w16, c = e - r * w16;
-            float g = 0.0f;
-            if (c < W && cur[r * pitch + c] > 0.0f) g = dys[r] * Wo[c];
-            cur[r * pitch + c] = g;
-            if (c < W && r0 + r < a.n) a.dz[((int64_t)(a.depth - 1) * a.n + r0 + r) * W + c] = g;
-        }
+        for (int r = wave; r < R; r += 8)
+            for (int c = lane; c < w16; c += 64) cur[r * pitch + c] = cur[r * pitch + c] > 0.0f ? dys[r] * wo[c] : 0.0f;
         __syncthreads();
         for (int l = a.depth - 1; l > 0; --l) {
             float* prev = cur - bufsz;                       // activations below layer l, then their gradients
             if (c0 < w16) {
-                product(cur, p1 + (l - 1) * lsz, W, std::integral_constant<bool, true>{});
+                product(cur, p1 + (l - 1) * lsz, W, back);
+                if (l > 1) weights(p1 + (l - 2) * lsz, W, 0, back);
 #pragma unroll
                 for (int j = 0; j < CT; ++j) {
-                    const int col = c0 + 16 * j + sub;
-                    if (col >= w16) continue;
+                    if (c0 + 16 * j >= w16) continue;
+                    float* at = prev + 4 * grp * pitch + lds_col(c0 + 16 * j + sub);
 #pragma unroll
                     for (int i = 0; i < RT; ++i)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            const int r = 16 * i + 4 * grp + e;
-                            const float g = prev[r * pitch + col] > 0.0f ? acc[i][j][e] : 0.0f;
-                            prev[r * pitch + col] = g;
-                            if (col < W && r0 + r < a.n) a.dz[((int64_t)(l - 1) * a.n + r0 + r) * W + col] = g;
+                            float& v = at[(16 * i + e) * pitch];
+                            v = v > 0.0f ? acc[i][j][e] : 0.0f;
                         }
                 }
             }
             cur = prev;
             __syncthreads();
         }
+        for (int l = 0; l < a.depth; ++l) save(lds + (l + 1) * bufsz, a.dz + (int64_t)l * a.n * W, W);
     }
 }
 
-// Weight and bias gradients of layers [l0, l0 + count): dW[o][i] =
-// sum_r dZ[r][o] A[r][i], db[o] = sum_r dZ[r][o], accumulated in FP64 on the
-// matrix cores (v_mfma_f64_16x16x4f64; products of two floats are exact).
-// Block (tile, split): 64 x 64 weights over one range of rows, a wave 32 x 32
-// of them read straight from the row-major operands (64-byte runs).  Bound: the
-// row range's loads.  A training step of 4096 rows, 36 -> 128 x 3 -> 1: 6137 us
-// with one thread per weight summing all rows, 54 us with this launch and the
-// fused one (three launches instead of 15).
-struct GradLayer {
-    const float *dz, *act;
-    int64_t w_off, b_off;
-    int dout, din, tile0;          // first tile of the layer
-};
+// Weight and bias gradients of all layers: dW[o][i] = sum_r dZ[r][o] A[r][i],
+// db[o] = sum_r dZ[r][o], accumulated in FP64 on the matrix cores
+// (v_mfma_f64_16x16x4f64; products of two floats are exact).  Block (tile,
+// split): 64 x 64 weights over one range of rows, a wave 32 x 32 of them read
+// straight from the row-major operands (64-byte runs), the next rows' loads in
+// flight during these rows' products.  Bound: the FP64 pipes (half as many blocks
+// of twice the rows take the same time).  A training step of 4096 rows,
+// 36 -> 128 x 3 -> 1: 6137 us with one thread per weight summing all rows, 50 us
+// with this launch (21 us of it; 27.7 with conditional loads that were waited for
+// one by one) and the fused one (three launches instead of 15).
 struct GradArgs {
-    GradLayer layer[17];
-    int n_layers, splits;
-    int64_t n, rows, P;            // rows: rows of a split
-    float* grads;                  // splits == 1: written here
-    double* part;                  // else: partials [split][P]
+    const float *xn, *acts, *dy, *dz;      // acts, dz: hidden layers after one another
+    int n_in, width, depth, splits;
+    int64_t n, rows, P;                    // rows: rows of a split
+    float* grads;                          // splits == 1: written here
+    double* part;                          // else: partials [split][P]
 };
 
 __global__ __launch_bounds__(256) void k_mlp_wgrad(GradArgs a) {
+    // The tiles of a row range run on one of the eight XCDs (blocks go to them in
+    // turn), so its rows come from memory once.
+    const int b = blockIdx.x, per = (int)gridDim.x / a.splits;
+    const bool by8 = a.splits % 8 == 0;
+    const int split = by8 ? (b >> 3) / per * 8 + (b & 7) : b / per;
+    int t = by8 ? (b >> 3) % per : b % per;
+    // layers in order: n_in -> width, the hidden ones, width -> 1
+    const int W = a.width, tw = (W + kGradTile - 1) / kGradTile, ti = (a.n_in + kGradTile - 1) / kGradTile;
     int l = 0;
-    while (l + 1 < a.n_layers && (int)blockIdx.x >= a.layer[l + 1].tile0) ++l;
-    const GradLayer& L = a.layer[l];
-    const int t = (int)blockIdx.x - L.tile0;
-    const int ti_n = (L.din + kGradTile - 1) / kGradTile;
+    if (t >= tw * ti) {
+        t -= tw * ti;
+        l = 1 + t / (tw * tw) < a.depth ? 1 + t / (tw * tw) : a.depth;
+        t -= (l - 1) * tw * tw;
+    }
+    const int din = l == 0 ? a.n_in : W, dout = l == a.depth ? 1 : W;
+    const int64_t w_off = l == 0 ? 0 : (int64_t)W * (a.n_in + 1) + (int64_t)(l - 1) * W * (W + 1);
+    const int64_t b_off = w_off + (int64_t)din * dout;
+    const int ti_n = l == 0 ? ti : tw;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int o0 = t / ti_n * kGradTile + 32 * (wave >> 1), i0 = t % ti_n * kGradTile + 32 * (wave & 1);
-    if (o0 >= L.dout || i0 >= L.din) return;
+    if (o0 >= dout || i0 >= din) return;
     const int sub = lane & 15, grp = lane >> 4;
-    const int64_t rb = (int64_t)blockIdx.y * a.rows;
+    const int64_t rb = (int64_t)split * a.rows;
     const int64_t re = rb + a.rows < a.n ? rb + a.rows : a.n;
-    const float* __restrict__ dz = L.dz;
-    const float* __restrict__ act = L.act;
-    const bool ov[2] = {o0 + sub < L.dout, o0 + 16 + sub < L.dout};
-    const bool iv[2] = {i0 + sub < L.din, i0 + 16 + sub < L.din};
-    const bool two_o = o0 + 16 < L.dout, two_i = i0 + 16 < L.din;
+    const float* __restrict__ dz = l == a.depth ? a.dy : a.dz + l * a.n * W;
+    const float* __restrict__ act = l == 0 ? a.xn : a.acts + (l - 1) * a.n * W;
+    const bool ov[2] = {o0 + sub < dout, o0 + 16 + sub < dout};
+    const bool iv[2] = {i0 + sub < din, i0 + 16 + sub < din};
+    // every lane loads (conditional loads were waited for one by one): columns past
+    // the layer repeat its last one, rows past the range its first
+    const int oc[2] = {o0 + sub < dout ? o0 + sub : dout - 1, o0 + 16 + sub < dout ? o0 + 16 + sub : dout - 1};
+    const int ic[2] = {i0 + sub < din ? i0 + sub : din - 1, i0 + 16 + sub < din ? i0 + 16 + sub : din - 1};
+    const bool two_o = o0 + 16 < dout, two_i = i0 + 16 < din;
     v4d acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -511,21 +592,26 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(GradArgs a) {
         for (int j = 0; j < 2; ++j) acc[i][j] = v4d{0, 0, 0, 0};
     double bs[2] = {0.0, 0.0};
     constexpr int U = 8;           // row groups of 4 whose loads are in flight together
-    for (int64_t r = rb; r < re; r += 4 * U) {
-        float x[U][2], y[U][2];
+    auto load = [&](int64_t r, float (&x)[U][2], float (&y)[U][2]) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t row = r + 4 * u + grp;
-            const bool rv = row < re;
+            const int64_t at = r + 4 * u + grp, row = at < re ? at : rb;
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
-                x[u][q] = rv && ov[q] ? dz[row * L.dout + o0 + 16 * q + sub] : 0.0f;
-                y[u][q] = rv && iv[q] ? act[row * L.din + i0 + 16 * q + sub] : 0.0f;
+                x[u][q] = dz[row * dout + oc[q]];
+                y[u][q] = act[row * din + ic[q]];
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](int64_t r, const float (&x)[U][2], const float (&y)[U][2]) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const double xd[2] = {(double)x[u][0], (double)x[u][1]}, yd[2] = {(double)y[u][0], (double)y[u][1]};
+            if (r + 4 * u >= re) break;
+            // (columns past the layer are not written: only rows past the range are zeroed)
+            const bool rv = r + 4 * u + grp < re;
+            const double xd[2] = {rv ? (double)x[u][0] : 0.0, rv ? (double)x[u][1] : 0.0};
+            const double yd[2] = {rv ? (double)y[u][0] : 0.0, rv ? (double)y[u][1] : 0.0};
             bs[0] += xd[0];
             bs[1] += xd[1];
             acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(xd[0], yd[0], acc[0][0], 0, 0, 0);
@@ -533,8 +619,17 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(GradArgs a) {
             if (two_o) acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(xd[1], yd[0], acc[1][0], 0, 0, 0);
             if (two_o && two_i) acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(xd[1], yd[1], acc[1][1], 0, 0, 0);
         }
+    };
+    // the next 4 U rows are loaded during the products of these
+    float x0[U][2], y0[U][2], x1[U][2], y1[U][2];
+    if (rb < re) load(rb, x0, y0);
+    for (int64_t r = rb; r < re; r += 8 * U) {
+        load(r + 4 * U, x1, y1);
+        multiply(r, x0, y0);
+        load(r + 8 * U, x0, y0);
+        multiply(r + 4 * U, x1, y1);
     }
-    double* part = a.part + (int64_t)blockIdx.y * a.P;
+    double* part = a.part + (int64_t)split * a.P;
     auto put = [&](int64_t at, double v) {
         if (a.splits == 1) a.grads[at] = (float)v;
         else part[at] = v;
@@ -547,14 +642,14 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(GradArgs a) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int o = o0 + 16 * i + grp + 4 * e;
-                if (o < L.dout && iv[j]) put(L.w_off + (int64_t)o * L.din + i0 + 16 * j + sub, acc[i][j][e]);
+                if (o < dout && iv[j]) put(w_off + (int64_t)o * din + i0 + 16 * j + sub, acc[i][j][e]);
             }
     if (i0 == 0) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             bs[i] += __shfl_xor(bs[i], 16);
             bs[i] += __shfl_xor(bs[i], 32);
-            if (grp == 0 && ov[i]) put(L.b_off + o0 + 16 * i + sub, bs[i]);
+            if (grp == 0 && ov[i]) put(b_off + o0 + 16 * i + sub, bs[i]);
         }
     }
 }
@@ -691,26 +786,21 @@ static void gradients(const MlpLayout& L, float* state, const float* x, const fl
         }
     }
     GradArgs g{};
-    g.n_layers = L.n_layers;
+    g.xn = a.xn;
+    g.acts = a.acts;
+    g.dy = a.dy;
+    g.dz = a.dz;
+    g.n_in = L.n_in;
+    g.width = L.width;
+    g.depth = L.depth;
     g.splits = (int)grad_splits(L, n);
     g.n = n;
+    if (g.splits >= 8) g.splits &= ~7;      // as many ranges on each XCD
     g.rows = (n + g.splits - 1) / g.splits;
     g.P = L.P;
     g.grads = state + L.grads_off;
     g.part = (double*)(ws + o.grad);
-    int tiles = 0;
-    for (int l = 0; l < L.n_layers; ++l) {
-        GradLayer& q = g.layer[l];
-        q.dz = l == L.depth ? a.dy : a.dz + (int64_t)l * n * L.width;
-        q.act = l == 0 ? a.xn : a.acts + (int64_t)(l - 1) * n * L.width;
-        q.w_off = L.w_off[l];
-        q.b_off = L.b_off[l];
-        q.dout = L.dout[l];
-        q.din = L.din[l];
-        q.tile0 = tiles;
-        tiles += ((q.dout + kGradTile - 1) / kGradTile) * ((q.din + kGradTile - 1) / kGradTile);
-    }
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)tiles, (unsigned)g.splits), dim3(256), 0, s, g);
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)(grad_tiles(L) * g.splits)), dim3(256), 0, s, g);
     hipLaunchKernelGGL(k_mlp_reduce, dim3(nblk(L.P, 256) + 1), dim3(256), 0, s, g.part, g.splits, L.P, g.grads,
                        params, state + L.m_off, state + L.v_off, adam ? 1 : 0, adam ? *adam : AdamArgs{}, lpart,
                        (int)nb, n, loss);
