@@ -339,7 +339,10 @@ constexpr int kSplitDefaultMax = 16;
 // outputs over 2^21 terms) run as tile jobs split over up to this many blocks
 // (each part at least 2^kSplitMinPartLog terms, S x tiles <= kSplitMaxTiles);
 // the small kernel's block per output would stream a whole row and column of
-// the operands per output.
+// the operands per output.  From 2^17 terms and 64 outputs on also where slices
+// fill only part of a tile (8 x 16 outputs over 2^21 terms, twice: 1306 us on the
+// small kernel, 924 us split; 8 x 16 over 2^17 40 us less; at 2^14 and 2^15 terms
+// 8 x 16 outputs took 7 to 15 us more, 32 x 16 6 us less).
 constexpr int kSplitLongMax = 512;
 // A matrix-core job with at most this share of the flops of its level's main
 // tile shape takes that shape, so that it runs in the main launch.
@@ -1170,8 +1173,8 @@ struct Builder {
             const bool heavy = step_flops >= kMfmaMinFlops && rk <= (fp64 ? 8 : 11) && FA.size() + FB.size() >= 3;
             // tiny steps stay with their level's small-step launch even when
             // their shape would fill a tile: a launch of their own costs more
-            const bool long_sum = fp64 && rk > 8 && std::min(FA.size(), FB.size()) >= 5 &&
-                                  step_flops >= kMfmaMinFlops;
+            const bool long_sum = fp64 && rk > 8 && step_flops >= kMfmaMinFlops &&
+                                  (std::min(FA.size(), FB.size()) >= 5 || (rk >= 17 && FA.size() + FB.size() >= 6));
             bool to_tile = (big && step_flops >= kTileMinFlops) || heavy || long_sum;
             if (!fp64 && small_levels && small_levels->count(st.level)) to_tile = false;
             // inner sums under 8 terms would fill less than one staged chunk of a
