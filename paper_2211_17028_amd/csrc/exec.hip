@@ -652,7 +652,14 @@ struct Builder {
                        int64_t ninst, int64_t nbatch, PosIn posin, ByPos by_pos, SliceVec slice_vec, int fp64) {
         // FP64 steps run on the 64 x 64 or 32 x 32 FMA tiles (tile ids 1 and 4's shapes)
         const int64_t esz = fp64 ? 16 : 8;
-        static const double kEff[K_MFMA_TILES] = {1.0, 0.6, 0.75, 0.5, 0.35, 0.45, 0.3, 0.2};
+        // A tile's rate in a level, relative (order of the tile ids).  128 x 32 leads:
+        // full launches of it reach 93 to 98 % of the 128 x 64 tile's rate (86.8
+        // against 88.3 TFLOP/s over 256 terms), in half the work per tile, so a
+        // level's last round over the CUs is shorter.  Its entry was 0.75 when its
+        // waves held 64 rows; from there to 1, with 0.95 for 128 x 64: twelve packed
+        // circuits 2046 -> 1718 us, a range of 25-qubit amplitudes 1074 -> 1036,
+        // 25-qubit grid 1115 -> 1099, 36-qubit QAOA the same.
+        static const double kEff[K_MFMA_TILES] = {0.95, 0.6, 1.0, 0.5, 0.35, 0.45, 0.3, 0.2};
         static const double kEff64[K_MFMA_TILES] = {0, 1.0, 0, 0, 0.7, 0, 0, 0};
         const int rk = (int)K.size();
         const int64_t ns = ninst * nbatch;
