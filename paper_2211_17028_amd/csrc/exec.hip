@@ -1181,7 +1181,8 @@ struct Builder {
             // tiny steps stay with their level's small-step launch even when
             // their shape would fill a tile: a launch of their own costs more
             const bool long_sum = fp64 && rk > 8 && step_flops >= kMfmaMinFlops &&
-                                  (std::min(FA.size(), FB.size()) >= 5 || (rk >= 17 && FA.size() + FB.size() >= 6));
+                                  (std::min(FA.size(), FB.size()) >= 5 ||
+                                   (!ksplit_user && rk >= 17 && FA.size() + FB.size() >= 6));
             bool to_tile = (big && step_flops >= kTileMinFlops) || heavy || long_sum;
             if (!fp64 && small_levels && small_levels->count(st.level)) to_tile = false;
             // inner sums under 8 terms would fill less than one staged chunk of a
@@ -3661,10 +3662,18 @@ void tn_release_cached(void) {
 int tn_estimate_noalloc(int32_t n, const tn_plan* plans, const tn_terms* terms, void* stream, tn_result* results) {
     return guard([&] {
         if (!results) fail(TN_EINVAL, "null results");
-        std::unique_ptr<tn_exec_s> ex = build_exec(n, plans, terms, &estimate_opts(), TermRange{});
-        ex->results_stride = std::max<int64_t>(8, (ex->results_bytes + 7) & ~int64_t(7));
-        const size_t res_off = (size_t)round_up((int64_t)exec_need(ex.get()), 256);
-        const size_t need = res_off + (size_t)ex->results_stride;
+        std::unique_ptr<tn_exec_s> ex;
+        size_t res_off = 0, need = 0;
+        // above the fixed workspace: without the scratch of split sums
+        for (int split = 1; split >= 0; --split) {
+            tn_exec_opts o = estimate_opts();
+            if (!split) o.max_ksplit = 1;
+            ex = build_exec(n, plans, terms, &o, TermRange{});
+            ex->results_stride = std::max<int64_t>(8, (ex->results_bytes + 7) & ~int64_t(7));
+            res_off = (size_t)round_up((int64_t)exec_need(ex.get()), 256);
+            need = res_off + (size_t)ex->results_stride;
+            if (need <= kNoAllocScratchBytes) break;
+        }
         if (need > kNoAllocScratchBytes) {
             std::ostringstream os;
             os << "tn_estimate_noalloc: the estimate needs " << need << " bytes of workspace, above its fixed "
