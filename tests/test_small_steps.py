@@ -112,3 +112,20 @@ def test_joined_levels_are_independent_parts(case):
             for y in range(len(parts)):
                 if x != y:
                     assert not any(cut(s, t) for s in writes[x] for t in writes[y] + reads[y])
+
+
+@pytest.mark.parametrize("max_ksplit", [0, 1, 4])
+def test_long_sums_follow_the_callers_split_limit(max_ksplit):
+    """8 x 8 FP64 outputs over 2^18 terms: a split tile job, or the small-step
+    kernel where the caller limits the split."""
+    rng = np.random.default_rng(2)
+    gates = WC.grid_layers(4, 4, 18, "ABCD", rng)
+    kraus = [WC.kraus_ad_pd(*rng.uniform(1e-3, 1e-2, 2)) for _ in range(4)]
+    circ = WC.Circuit(16, WC.place_noises(gates, kraus, rng), WC.zero_product(16), "circuit_output",
+                      WC.zero_product(16), level=0)
+    plan = tn.tn_plan_build_doubled(circ, path_trials=256)
+    desc, _ = tn.tn_exec_describe_only([plan], [tn.tn_terms_enumerate(plan, 0)], tn.exec_opts(max_ksplit=max_ksplit))
+    tiled = [(j["m_log"], j["n_log"], j["k_log"]) for L in desc["launches"] if L.get("kernel") == "k_tile64_group"
+             for j in L["jobs"]]
+    small = [(j["m_log"], j["n_log"], j["k_log"]) for L in _groups(desc) for j in L["jobs"]]
+    assert ((3, 3, 18) in tiled) == (max_ksplit == 0) and ((3, 3, 18) in small) == (max_ksplit != 0)
