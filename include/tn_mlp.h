@@ -43,7 +43,8 @@ int tn_mlp_init(const tn_mlp_shape* s, uint64_t seed, void* d_state, void* strea
 int tn_mlp_fit_normalizer(const tn_mlp_shape* s, void* d_state, const float* d_x, int64_t n,
                           void* stream);
 
-/* d_y[n] = network(d_x[n x n_in]). */
+/* d_y[n] = network(d_x[n x n_in]).  d_y may lie over d_x or the workspace (the
+ * values then go through the workspace and one copy). */
 int tn_mlp_forward(const tn_mlp_shape* s, const void* d_state, const float* d_x, int64_t n,
                    float* d_y, void* d_ws, void* stream);
 

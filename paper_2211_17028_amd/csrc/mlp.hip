@@ -750,11 +750,24 @@ static void forward_layers(const MlpLayout& L, const float* state, const float* 
     }
 }
 
+static bool overlap(const float* a, int64_t na, const float* b, int64_t nb) {
+    const uintptr_t pa = (uintptr_t)a, pb = (uintptr_t)b;
+    return pa < pb + 4 * (uintptr_t)nb && pb < pa + 4 * (uintptr_t)na;
+}
+
+// A block writes its outputs while others still read their rows, the weights or
+// (layer by layer) the last activations: outputs that lie over any of these are
+// formed in the workspace and copied once every block is done.
 static void forward(const MlpLayout& L, const float* state, const float* x, int64_t n, float* ws, float* y,
                     hipStream_t s) {
+    const MlpWs o = ws_layout(L, n);
+    const bool over = overlap(y, n, x, n * L.n_in) || overlap(y, n, state, L.total) || overlap(y, n, ws, o.total);
+    // (the normalized rows are not read any more when the last layer runs)
+    float* out = !over ? y : ws + (overlap(y, n, ws + o.y, n) ? o.xn : o.y);
     MlpArgs a = mlp_args(L, state, x, n);
-    a.y = y;
-    if (!launch_fused<false>(L, a, s)) forward_layers(L, state, x, n, ws, y, s);
+    a.y = out;
+    if (!launch_fused<false>(L, a, s)) forward_layers(L, state, x, n, ws, out, s);
+    if (over) HIPCHK_M(hipMemcpyAsync(y, out, n * 4, hipMemcpyDeviceToDevice, s));
 }
 
 // loss and gradients, and with `adam` the update of the parameters
