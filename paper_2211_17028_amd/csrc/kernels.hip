@@ -745,58 +745,57 @@ void k_mfma_group(const MfmaJob* __restrict__ jobs, const MfmaTile* __restrict__
     // the MFMAs of the group before run (groups of four: up to 1.5 % slower).
     constexpr int RA = 2, G = BKC / RA;
     static_assert(G % 2 == 0, "the two operand sets alternate");
-    // column blocks of 16 holding outputs (padding is a suffix of the tile's
-    // columns: slices past cnt, columns past n): all TN, the first only, or none
-    int tn_act = 0;
+    // column blocks of 16 that a wave runs: those holding outputs in the block's first
+    // wave column (padding is a suffix of the tile's columns: slices past cnt, columns
+    // past n), all TN or the first only.  The second wave column of a 64-wide tile runs
+    // as many, on padding where the tile has at most 32 columns (a 32-wide tile's case).
+    // Every thread reads the same entries, so the choice is the same for the whole block.
+    // It is kept in a vector register: a scalar branch makes the accumulators 16 registers
+    // larger (108 against 92 on 128 x 32) and the 128 x 64 tile spills.
+    int tn_act = 1;
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-        if (col_c[wn * (TN * 16) + j * 16] >= 0) tn_act = j + 1;
+    for (int j = 1; j < TN; ++j)
+        if (col_c[j * 16] >= 0) tn_act = j + 1;
+    if (TN > 1) asm("" : "+v"(tn_act));
     const int64_t nchunks = c_end - c_begin;
     constexpr int WPP = (2 * AE + BE + RA - 1) / RA;      // LDS writes per inner index of a group
-    // The inner sum over TNA active column blocks.  Each wave takes one of the
-    // three forms as a whole, and all forms have one barrier per chunk.  (tn_act is
-    // not made a scalar: with scalar branches the accumulators are copied where the
-    // forms join, 28 more registers, and the 128 x 64 tile spills.)
+    // The inner sum over TNA column blocks.  The block takes one of two forms as a whole:
+    // each has the barriers of its chunks, so the choice may not differ between waves.
     auto sum = [&](auto tna) {
         constexpr int TNA = decltype(tna)::value;
-        constexpr int TB = TNA > 0 ? TNA : 1;
-        float a[2][RA][TM], b[2][RA][TB];
+        float a[2][RA][TM], b[2][RA][TNA];
         // operands of group g of the chunk in LDS buffer buf
-        auto read = [&](int buf, int g, float (&x)[RA][TM], float (&y)[RA][TB]) {
-            if constexpr (TNA > 0) {
-                const float* as = As + buf * ABUF + g * RA * AP;
-                const float* bs = Bs + buf * (BBUF + 2) + g * RA * BP;
+        auto read = [&](int buf, int g, float (&x)[RA][TM], float (&y)[RA][TNA]) {
+            const float* as = As + buf * ABUF + g * RA * AP;
+            const float* bs = Bs + buf * (BBUF + 2) + g * RA * BP;
 #pragma unroll
-                for (int p = 0; p < RA; ++p) {
+            for (int p = 0; p < RA; ++p) {
 #pragma unroll
-                    for (int i = 0; i < TM; ++i) x[p][i] = as[p * AP + a_off[i]];
+                for (int i = 0; i < TM; ++i) x[p][i] = as[p * AP + a_off[i]];
 #pragma unroll
-                    for (int j = 0; j < TNA; ++j) y[p][j] = bs[p * BP + b_off[j]];
-                }
-                __builtin_amdgcn_sched_barrier(0);         // ahead of the MFMAs that follow
+                for (int j = 0; j < TNA; ++j) y[p][j] = bs[p * BP + b_off[j]];
             }
+            __builtin_amdgcn_sched_barrier(0);             // ahead of the MFMAs that follow
         };
-        auto multiply = [&](const float (&x)[RA][TM], const float (&y)[RA][TB], bool staged) {
-            if constexpr (TNA > 0) {
+        auto multiply = [&](const float (&x)[RA][TM], const float (&y)[RA][TNA], bool staged) {
+#pragma unroll
+            for (int p = 0; p < RA; ++p) {
+                float z[TNA];
+#pragma unroll
+                for (int j = 0; j < TNA; ++j) z[j] = __uint_as_float(__float_as_uint(y[p][j]) ^ b_sign);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TNA; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[p][i], z[j], acc[i][j], 0, 0, 0);
+            }
+            if (staged) {
+                // the LDS writes and their VALU work between the MFMAs
 #pragma unroll
                 for (int p = 0; p < RA; ++p) {
-                    float z[TB];
-#pragma unroll
-                    for (int j = 0; j < TNA; ++j) z[j] = __uint_as_float(__float_as_uint(y[p][j]) ^ b_sign);
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < TNA; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[p][i], z[j], acc[i][j], 0, 0, 0);
-                }
-                if (staged) {
-                    // the LDS writes and their VALU work between the MFMAs
-#pragma unroll
-                    for (int p = 0; p < RA; ++p) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, TM * TNA, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x002, 3 * WPP, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x200, WPP, 0);
-                    }
+                    __builtin_amdgcn_sched_group_barrier(0x008, TM * TNA, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 3 * WPP, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x200, WPP, 0);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -838,9 +837,8 @@ void k_mfma_group(const MfmaJob* __restrict__ jobs, const MfmaTile* __restrict__
         }
         chunk(buf, no, no);
     };
-    if (tn_act == TN) sum(std::integral_constant<int, TN>{});
-    else if (TN > 1 && tn_act == 1) sum(std::integral_constant<int, 1>{});
-    else sum(std::integral_constant<int, 0>{});
+    if (TN == 1 || tn_act == TN) sum(std::integral_constant<int, TN>{});
+    else sum(std::integral_constant<int, 1>{});
 
     // split inner sum: this block's part goes to its row-major [BM][BNC] partial
     // tile (padding skipped), added to the others' by k_split_reduce
