@@ -666,8 +666,8 @@ void k_mfma_group(const MfmaJob* __restrict__ jobs, const MfmaTile* __restrict__
     int64_t akh = deposit(c_begin << kc_log, J.a_k, kc_log, k_log);
     int64_t bkh = deposit(c_begin << kc_log, J.b_k, kc_log, k_log);
     // this thread's staged elements in the first chunk (a chunk adds akh / bkh).
-    // Padding reads the operand's element 0 plus that offset, which is an element
-    // of its first instance, and is zeroed when staged (mask bits: q of A, 16 + q of B)
+    // Padding reads an element that the tile reads anyway (its first row or column,
+    // inner index 0 of a chunk) and is zeroed when staged (mask bits: q of A, 16 + q of B)
     const TN_GLOBAL float2* pa[AE];
     const TN_GLOBAL float2* pb[BE];
     uint32_t live = 0;
@@ -676,23 +676,17 @@ void k_mfma_group(const MfmaJob* __restrict__ jobs, const MfmaTile* __restrict__
         int r, p;
         a_rp(threadIdx.x + q * NT, r, p);
         const int64_t base = row_a[r];
-        const bool ok = base >= 0 && p < kc;
-        pa[q] = A + (ok ? base + ak_lo[p] : 0);
-        live |= ok ? 1u << q : 0u;
+        pa[q] = A + ((base >= 0 ? base : row_a[0]) + ak_lo[p]);
+        live |= base >= 0 && p < kc ? 1u << q : 0u;
     }
 #pragma unroll
     for (int q = 0; q < BE; ++q) {
         const int e = threadIdx.x + q * NT;
-        bool ok = false;
-        pb[q] = B;
-        if (e < BKC * BNC) {
-            int p, c;
-            b_pc(e, p, c);
-            const int64_t base = col_b[c];
-            ok = base >= 0 && p < kc;
-            if (ok) pb[q] = B + (base + bk_lo[p]);
-        }
-        live |= ok ? 1u << (16 + q) : 0u;
+        int p = 0, c = 0;
+        if (e < BKC * BNC) b_pc(e, p, c);
+        const int64_t base = col_b[c];
+        pb[q] = B + ((base >= 0 ? base : col_b[0]) + bk_lo[p]);
+        live |= e < BKC * BNC && base >= 0 && p < kc ? 1u << (16 + q) : 0u;
     }
     auto load = [&](float2* ra, float2* rb) {
 #pragma unroll
