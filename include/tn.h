@@ -264,6 +264,11 @@ int tn_terms_get(tn_terms terms, int8_t* patterns, double* weights);
  *   otherwise d_ws must hold >= *need_bytes bytes (else TN_ENOMEM); the upload
  *   is enqueued on `stream` and *out receives an executable handle bound to
  *   d_ws (the caller keeps d_ws alive and unmodified until tn_exec_destroy).
+ *   Below the size that the query reports, a schedule with less scratch for
+ *   split sums is tried before TN_ENOMEM; *need_bytes receives the size of the
+ *   schedule that is bound.  tn_estimate (before it goes to term ranges, and in
+ *   each of them), tn_contract_batch and tn_estimate_noalloc do the same.
+ *   Its sums are grouped otherwise, so values agree to rounding.
  *   With opts->tune = 1 the query reports the largest workspace of the
  *   schedules the autotuner times; a smaller d_ws that still holds the untuned
  *   schedule (the query with tune = 0) is accepted, and the autotuner then
@@ -390,16 +395,17 @@ void tn_release_cached(void);
 /* ---------------------------------------------------------------------------
  * tn_estimate_noalloc -- tn_estimate for callers that cannot allocate device
  * or page-locked memory (code under stream capture, tight serving loops,
- * harnesses that forbid hipMalloc): the same schedule and kernels, with the
- * workspace in a fixed 64 MiB device array of the library (one per GPU, held
- * until the process ends) instead of a caller buffer.  It calls no hipMalloc,
+ * harnesses that forbid hipMalloc): the schedule and kernels of tn_estimate with
+ * a 64 MiB workspace in which all terms run at once, here a fixed device array
+ * of the library (one per GPU, held until the process ends) instead of a caller
+ * buffer.  It calls no hipMalloc,
  * hipFree, hipHostMalloc, stream or event creation: the constants are copied
  * in, both chains and the tail run on `stream` one after the other, the level
  * sums are copied back, and the stream is synchronized.  Every call on a GPU
  * uses that GPU's array (its contents are rewritten by each call), so calls
  * that overlap on one GPU race: serialize them.  Not kept between calls.
  * Errors: TN_EINVAL (null handle or results), TN_ENOMEM (the estimate needs
- * more than the fixed 64 MiB; no device call is made), TN_EHIP.
+ * more than the fixed 64 MiB as one schedule; no device call is made), TN_EHIP.
  * ------------------------------------------------------------------------- */
 int tn_estimate_noalloc(int32_t n, const tn_plan* plans, const tn_terms* terms, void* stream,
                         tn_result* results);
@@ -509,8 +515,10 @@ int tn_plan_describe(tn_plan plan, char* buf, size_t* len);
 int tn_exec_describe(tn_exec ex, char* buf, size_t* len);
 
 /* The staged constant region of a prepared (or size-queried) schedule: fixed
- * tensors, slot tensors, instance maps and permutation tables, exactly as
- * uploaded to the start of the workspace.  Host only; *len receives the size. */
+ * tensors, slot tensors, instance maps and permutation tables as uploaded to the
+ * start of the workspace, then zeros in the place of the buffers that the device
+ * writes before it reads them (of those only the per-term outputs are uploaded,
+ * when the schedule is bound).  Host only; *len receives the size. */
 int tn_exec_const_bytes(tn_exec ex, void* buf, size_t* len);
 
 void tn_plan_destroy(tn_plan plan);

@@ -248,6 +248,7 @@ struct tn_exec_s {
     std::vector<tn::Launch> tail;           // finalize + level sums
     std::vector<tn::Chain> chains;
     bool probe = false;                     // built for its shapes only (see build_exec)
+    bool narrow = false;                    // split sums with less scratch (see build_fitting)
     // packed circuits: the tail runs as one finalize and one level-sum launch
     // the tail of all packed circuits: one record per circuit, the per-block
     // level partials of the term launch
@@ -551,6 +552,7 @@ struct Builder {
     bool quantize_tiles = true;  // tile model: whole rounds over the CUs (one circuit)
     int max_ksplit = kSplitDefaultMax;  // largest split of a tile job's inner sum (1 = none)
     bool ksplit_user = false;            // max_ksplit set by the caller (applies to every job)
+    bool narrow = false;                 // for a small workspace (see build_fitting)
     // FP32 tile shape imposed per tree level on jobs of at most the given
     // flops (the small jobs join the level's main matrix-core launch)
     const std::map<int, std::pair<int, double>>* level_tile = nullptr;
@@ -659,7 +661,11 @@ struct Builder {
         // waves held 64 rows; from there to 1, with 0.95 for 128 x 64: twelve packed
         // circuits 2046 -> 1718 us, a range of 25-qubit amplitudes 1074 -> 1036,
         // 25-qubit grid 1115 -> 1099, 36-qubit QAOA the same.
-        static const double kEff[K_MFMA_TILES] = {0.95, 0.6, 1.0, 0.5, 0.35, 0.45, 0.3, 0.2};
+        static const double kEffWide[K_MFMA_TILES] = {0.95, 0.6, 1.0, 0.5, 0.35, 0.45, 0.3, 0.2};
+        // for a small workspace (build_fitting): 128 x 32 is taken less often, whose
+        // split sums need more scratch than the smaller tiles'
+        static const double kEffNarrow[K_MFMA_TILES] = {1.0, 0.6, 0.75, 0.5, 0.35, 0.45, 0.3, 0.2};
+        const double* kEff = narrow ? kEffNarrow : kEffWide;
         static const double kEff64[K_MFMA_TILES] = {0, 1.0, 0, 0, 0.7, 0, 0, 0};
         const int rk = (int)K.size();
         const int64_t ns = ninst * nbatch;
@@ -1182,7 +1188,7 @@ struct Builder {
             // their shape would fill a tile: a launch of their own costs more
             const bool long_sum = fp64 && rk > 8 && step_flops >= kMfmaMinFlops &&
                                   (std::min(FA.size(), FB.size()) >= 5 ||
-                                   (!ksplit_user && rk >= 17 && FA.size() + FB.size() >= 6));
+                                   (!ksplit_user && !narrow && rk >= 17 && FA.size() + FB.size() >= 6));
             bool to_tile = (big && step_flops >= kTileMinFlops) || heavy || long_sum;
             if (!fp64 && small_levels && small_levels->count(st.level)) to_tile = false;
             // inner sums under 8 terms would fill less than one staged chunk of a
@@ -1766,6 +1772,7 @@ static void build_schedule(tn_exec_s* ex, int n, const tn_plan* plans, const tn_
     bw.small_levels = small_levels;
     bw.grouping = ex->opts.no_group == 0;
     bw.quantize_tiles = n == 1;
+    bw.narrow = ex->narrow;
     if (ex->opts.max_ksplit > 0) {
         bw.max_ksplit = std::min(ex->opts.max_ksplit, 32);
         bw.ksplit_user = true;
@@ -2647,11 +2654,12 @@ static void fill_results(tn_exec_s* ex, const void* base, tn_result* results) {
 // Host part of tn_exec_prepare: the schedule of n packed plans over the terms
 // in `range`, with its constant region staged on the host (no device call).
 static std::unique_ptr<tn_exec_s> build_exec(int n, const tn_plan* plans, const tn_terms* terms,
-                                             const tn_exec_opts* opts, TermRange range) {
+                                             const tn_exec_opts* opts, TermRange range, bool narrow = false) {
     if (n < 1 || !plans || !terms) fail(TN_EINVAL, "need at least one plan with its terms");
     for (int i = 0; i < n; ++i)
         if (!plans[i] || !terms[i]) fail(TN_EINVAL, "null plan or term handle");
     auto ex = std::make_unique<tn_exec_s>();
+    ex->narrow = narrow;
     if (opts) ex->opts = *opts;
     else {
         ex->opts.mode = TN_MODE_BATCHED;
@@ -2681,6 +2689,7 @@ static std::unique_ptr<tn_exec_s> build_exec(int n, const tn_plan* plans, const 
         tn_exec_s probe;
         probe.opts = ex->opts;
         probe.probe = true;
+        probe.narrow = ex->narrow;
         build_schedule(&probe, n, plans, terms, nullptr, range);
         std::map<int, std::map<int, double>> flops;   // level -> tile -> flops
         std::map<int, double> level_flops;            // level -> FP32 flops
@@ -2717,6 +2726,27 @@ static std::unique_ptr<tn_exec_s> build_exec(int n, const tn_plan* plans, const 
 }
 
 static size_t exec_need(const tn_exec_s* ex) { return (size_t)(ex->const_bytes + ex->work_bytes); }
+
+// the same with the results behind the schedule
+static size_t exec_need_with_results(const tn_exec_s* ex) {
+    return (size_t)(round_up((int64_t)exec_need(ex), 256) + std::max<int64_t>(8, round_up(ex->results_bytes, 8)));
+}
+
+// The schedule for a workspace of `avail` bytes: where the model's own needs
+// more, the narrow one, if that needs less (128 x 32 tiles and split FP64 sums
+// taken less often: up to 15 % less in circuits whose split scratch is much of
+// their peak, an 86- and a 38-qubit chain 41 -> 36 and 61 -> 51 MB).
+static std::unique_ptr<tn_exec_s> build_fitting(int n, const tn_plan* plans, const tn_terms* terms,
+                                                const tn_exec_opts* opts, TermRange range, size_t avail,
+                                                size_t (*need)(const tn_exec_s*) = exec_need) {
+    std::unique_ptr<tn_exec_s> ex = build_exec(n, plans, terms, opts, range);
+    bool tiles = false;                        // without tile jobs both are the same
+    for (auto* list : {&ex->launches_const, &ex->launches, &ex->launches64})
+        for (const Launch& L : *list) tiles = tiles || L.kind == L_MGROUP;
+    if (need(ex.get()) <= avail || !tiles) return ex;
+    std::unique_ptr<tn_exec_s> small = build_exec(n, plans, terms, opts, range, true);
+    return need(small.get()) < need(ex.get()) ? std::move(small) : std::move(ex);
+}
 
 // Autotuner of the grouped matrix-core launches (one plan).  For every FP32
 // tree level with tile launches, in level order, the schedule with the model's
@@ -2761,6 +2791,7 @@ static size_t tune_need(const tn_exec_s* ex, int n, const tn_plan* plans, const 
             lt[lv] = {tile, INFINITY};
             tn_exec_s cand;
             cand.opts = ex->opts;
+            cand.narrow = ex->narrow;
             build_schedule(&cand, n, plans, terms, &lt, range,
                            ex->small_levels.empty() ? nullptr : &ex->small_levels);
             need = std::max(need, exec_need(&cand));
@@ -2787,6 +2818,7 @@ static std::unique_ptr<tn_exec_s> tune_grouped(std::unique_ptr<tn_exec_s> ex, in
         cand->opts.tune = 0;
         cand->opts.time_kernels = 0;
         cand->opts.use_graph = 0;
+        cand->narrow = ex->narrow;
         cand->small_levels = ex->small_levels;
         cand->level_tile = lt;
         build_schedule(cand.get(), n, plans, terms, &lt, range, small);
@@ -2843,6 +2875,7 @@ static std::unique_ptr<tn_exec_s> tune_grouped(std::unique_ptr<tn_exec_s> ex, in
     }
     auto tuned = std::make_unique<tn_exec_s>();
     tuned->opts = ex->opts;
+    tuned->narrow = ex->narrow;
     tuned->small_levels = ex->small_levels;
     tuned->level_tile = ex->level_tile;
     for (auto& kv : chosen) tuned->level_tile[kv.first] = kv.second;
@@ -2870,7 +2903,7 @@ static void bind_exec(tn_exec_s* ex, void* d_ws, size_t ws_bytes, hipStream_t st
     ex->base = (char*)d_ws;
     ex->stream = stream;
     HIPCHK(hipGetDevice(&ex->device));
-    ex->results_stride = std::max<int64_t>(8, (ex->results_bytes + 7) & ~int64_t(7));
+    ex->results_stride = std::max<int64_t>(8, round_up(ex->results_bytes, 8));
     HIPCHK(hipHostMalloc(&ex->results_host, (size_t)(3 * ex->results_stride),
                          hipHostMallocMapped | hipHostMallocCoherent));
     HIPCHK(hipHostGetDevicePointer(&ex->results_dev, ex->results_host, 0));
@@ -3069,11 +3102,11 @@ static size_t min_workspace(int n, const tn_plan* plans, const tn_terms* terms) 
         if (!plans[i] || !terms[i]) fail(TN_EINVAL, "null plan or term handle");
         const Terms& T = *reinterpret_cast<const Terms*>(terms[i]);
         size_t m = 0;
-        if (T.n > 0) m = exec_need(build_exec(1, &plans[i], &terms[i], &estimate_opts(), TermRange{0, 1}).get());
+        if (T.n > 0) m = exec_need(build_fitting(1, &plans[i], &terms[i], &estimate_opts(), TermRange{0, 1}, 0).get());
         for (int64_t t = 1; t < T.n; ++t)
             if (!T.zero[t] && !T.pruned[t]) {
-                m = std::max(m, exec_need(build_exec(1, &plans[i], &terms[i], &estimate_opts(),
-                                                     TermRange{t, t + 1}).get()));
+                m = std::max(m, exec_need(build_fitting(1, &plans[i], &terms[i], &estimate_opts(),
+                                                        TermRange{t, t + 1}, 0).get()));
                 break;
             }
         mx = std::max(mx, (size_t)chunk_acc_bytes(T) + m);
@@ -3101,7 +3134,7 @@ static void estimate_chunked(int n, const tn_plan* plans, const tn_terms* terms,
             cnt = std::min(cnt, T.n - lo);
             std::unique_ptr<tn_exec_s> ex;
             for (;;) {
-                ex = build_exec(1, &plans[i], &terms[i], &estimate_opts(), TermRange{lo, lo + cnt});
+                ex = build_fitting(1, &plans[i], &terms[i], &estimate_opts(), TermRange{lo, lo + cnt}, avail);
                 if (exec_need(ex.get()) <= avail) break;
                 if (cnt == 1) fail(TN_ENOMEM, "one term's schedule does not fit the workspace");
                 cnt = (cnt + 1) / 2;
@@ -3327,7 +3360,8 @@ void tn_terms_destroy(tn_terms terms) {
 int tn_exec_prepare(int32_t n, const tn_plan* plans, const tn_terms* terms, const tn_exec_opts* opts,
                     void* d_ws, size_t ws_bytes, void* stream, size_t* need_bytes, tn_exec* out) {
     return guard([&] {
-        std::unique_ptr<tn_exec_s> ex = build_exec(n, plans, terms, opts, TermRange{});
+        // (ws_bytes == 0, the size query: the model's own schedule)
+        std::unique_ptr<tn_exec_s> ex = build_fitting(n, plans, terms, opts, TermRange{}, ws_bytes ? ws_bytes : SIZE_MAX);
         const size_t need = ex->opts.tune ? tune_need(ex.get(), n, plans, terms, TermRange{}) : exec_need(ex.get());
         if (need_bytes) *need_bytes = need;
         if (ws_bytes == 0) {
@@ -3586,7 +3620,7 @@ int tn_estimate(int32_t n, const tn_plan* plans, const tn_terms* terms, void* d_
         std::lock_guard<std::mutex> lk(cache_mutex());
         CachedExec* ce = cache_find(0, n, plans, terms, TermRange{}, d_ws, ws_bytes);
         if (!ce) {
-            std::unique_ptr<tn_exec_s> ex = build_exec(n, plans, terms, &estimate_opts(), TermRange{});
+            std::unique_ptr<tn_exec_s> ex = build_fitting(n, plans, terms, &estimate_opts(), TermRange{}, ws_bytes);
             if (exec_need(ex.get()) > ws_bytes) {
                 // below the one-schedule size: term ranges one after another
                 const size_t mn = min_workspace(n, plans, terms);
@@ -3631,7 +3665,7 @@ int tn_contract_batch(int32_t n, const tn_plan* plans, const tn_terms* terms, in
         std::lock_guard<std::mutex> lk(cache_mutex());
         CachedExec* ce = cache_find(1, n, plans, terms, range, d_ws, ws_bytes);
         if (!ce) {
-            std::unique_ptr<tn_exec_s> ex = build_exec(n, plans, terms, &batch_opts(), range);
+            std::unique_ptr<tn_exec_s> ex = build_fitting(n, plans, terms, &batch_opts(), range, ws_bytes);
             if (exec_need(ex.get()) > ws_bytes) {
                 std::ostringstream os;
                 os << "workspace too small for terms [" << first << ", " << first + count << "): " << ws_bytes
@@ -3662,18 +3696,10 @@ void tn_release_cached(void) {
 int tn_estimate_noalloc(int32_t n, const tn_plan* plans, const tn_terms* terms, void* stream, tn_result* results) {
     return guard([&] {
         if (!results) fail(TN_EINVAL, "null results");
-        std::unique_ptr<tn_exec_s> ex;
-        size_t res_off = 0, need = 0;
-        // above the fixed workspace: without the scratch of split sums
-        for (int split = 1; split >= 0; --split) {
-            tn_exec_opts o = estimate_opts();
-            if (!split) o.max_ksplit = 1;
-            ex = build_exec(n, plans, terms, &o, TermRange{});
-            ex->results_stride = std::max<int64_t>(8, (ex->results_bytes + 7) & ~int64_t(7));
-            res_off = (size_t)round_up((int64_t)exec_need(ex.get()), 256);
-            need = res_off + (size_t)ex->results_stride;
-            if (need <= kNoAllocScratchBytes) break;
-        }
+        std::unique_ptr<tn_exec_s> ex = build_fitting(n, plans, terms, &estimate_opts(), TermRange{},
+                                                      kNoAllocScratchBytes, exec_need_with_results);
+        const size_t need = exec_need_with_results(ex.get()), res_off = round_up((int64_t)exec_need(ex.get()), 256);
+        ex->results_stride = (int64_t)(need - res_off);
         if (need > kNoAllocScratchBytes) {
             std::ostringstream os;
             os << "tn_estimate_noalloc: the estimate needs " << need << " bytes of workspace, above its fixed "
