@@ -68,19 +68,49 @@ static MlpLayout layout_of(const tn_mlp_shape* s) {
     return L;
 }
 
-// Output tiles of the weight-gradient launch (64 x 64 weights each) and the
-// number of row ranges a batch of n is split over: enough blocks for two per
-// CU, at least 64 rows each.  One range writes the gradients directly, more
-// write FP64 partials that the reduction adds in range order.
+// The fused launch serves networks whose layers a block's eight waves hold in
+// registers (up to 256 columns) and whose rows fit 64 KB of LDS; others go
+// layer by layer.  Rows per block: 64 for the most reuse of a block's weight
+// reads, fewer while that leaves CUs without a block.  Returns the LDS bytes of
+// a block of 16 rt rows, 0 if the shape is not served.
+static size_t fused_lds(const MlpLayout& L, int rt, bool train, int* pitch) {
+    const int cols = (std::max(L.n_in, L.width) + 15) / 16 * 16;
+    *pitch = cols + 4;      // rows start 4 LDS banks apart: conflict-free 16-byte reads
+    const size_t b = (size_t)16 * rt * *pitch * 4 * (train ? L.depth + 1 : 1);
+    return cols <= 256 && b <= 60 * 1024 ? b : 0;
+}
+
+// Output tiles of a weight-gradient launch (64 x 64 weights each; of all layers,
+// layer < 0, or of one) and the number of row ranges a batch of n is split over:
+// enough blocks for two per CU, at least 64 rows each.  One range writes the
+// gradients directly, more write FP64 partials that the reduction adds in range
+// order.
 constexpr int kGradTile = 64;
-static int64_t grad_tiles(const MlpLayout& L) {
+static int64_t grad_tiles(const MlpLayout& L, int layer) {
     int64_t t = 0;
     for (int l = 0; l < L.n_layers; ++l)
-        t += (int64_t)((L.dout[l] + kGradTile - 1) / kGradTile) * ((L.din[l] + kGradTile - 1) / kGradTile);
+        if (layer < 0 || l == layer)
+            t += (int64_t)((L.dout[l] + kGradTile - 1) / kGradTile) * ((L.din[l] + kGradTile - 1) / kGradTile);
     return t;
 }
-static int64_t grad_splits(const MlpLayout& L, int64_t n) {
-    return std::max<int64_t>(1, std::min<int64_t>(512 / grad_tiles(L), n / 64));
+static int64_t grad_splits(const MlpLayout& L, int64_t n, int layer) {
+    const int64_t s = std::max<int64_t>(1, std::min<int64_t>(512 / grad_tiles(L, layer), n / 64));
+    return s >= 8 ? s & ~int64_t(7) : s;     // as many ranges on each XCD
+}
+static int64_t layer_params(const MlpLayout& L, int l) { return (int64_t)L.dout[l] * (L.din[l] + 1); }
+
+// Layer by layer, the pre-activations' gradients of more hidden layers than two
+// are kept for one weight-gradient launch over all layers while they take up to
+// 256 MB more than two would.  Above that a layer's weight gradients are formed
+// before its inputs' gradients, which then take the place of its inputs (16
+// hidden layers of 1024, 65536 rows: 8.6 GB of workspace, 4.3 GB so).  Below, the
+// launches per layer are not worth it (6 hidden layers of 272, 16000 rows, a step
+// 2993 us kept, 3058 in place; 5 of 1024, 8192 rows 13615 and 13053).
+constexpr int64_t kKeptGradFloats = 64 << 20;
+static int64_t in_place_from(const MlpLayout& L) {      // smallest such batch
+    int pitch;
+    if (L.depth <= 2 || fused_lds(L, 1, true, &pitch)) return INT64_MAX;
+    return kKeptGradFloats / ((int64_t)(L.depth - 2) * L.width) + 1;
 }
 
 // Workspace of a batch of n (float offsets): normalized input, activations of
@@ -98,11 +128,22 @@ static MlpWs ws_layout(const MlpLayout& L, int64_t n) {
     w.y = up(w.acts + (int64_t)L.depth * n * L.width);
     w.dy = up(w.y + n);
     w.dz = up(w.dy + n);
-    w.part = up(w.dz + (int64_t)L.depth * n * L.width);
+    const bool in_place = n >= in_place_from(L);
+    if (in_place) w.dz = w.acts;
+    w.part = in_place ? up(w.dy + n) : up(w.dz + (int64_t)L.depth * n * L.width);
     w.grad = up(w.part + 2 * ((n + 15) / 16));
-    const int64_t S = grad_splits(L, n);
-    w.total = up(w.grad + (S > 1 ? 2 * S * L.P : 0));
+    int64_t partials = 0;                               // FP64, of the ranges that run together
+    for (int l = in_place ? 0 : -1; l < (in_place ? L.n_layers : 0); ++l) {
+        const int64_t S = grad_splits(L, n, l);
+        if (S > 1) partials = std::max(partials, S * (l < 0 ? L.P : layer_params(L, l)));
+    }
+    w.total = up(w.grad + 2 * partials);
     return w;
+}
+// floats that hold every batch up to n
+static int64_t ws_floats(const MlpLayout& L, int64_t n) {
+    const int64_t m = in_place_from(L) - 1;
+    return std::max(ws_layout(L, n).total, n > m ? ws_layout(L, m).total : 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -211,9 +252,9 @@ __global__ __launch_bounds__(256) void k_loss_grad(const float* y, const float* 
 }
 
 // dX[n x din] = (dZ[n x dout] W) * (A_prev > 0): gradient through a layer and
-// the previous layer's ReLU (A_prev is that layer's output)
+// the previous layer's ReLU (A_prev is that layer's output; dX may replace it)
 __global__ __launch_bounds__(256) void k_linear_bwd_data(const float* __restrict__ dZ, const float* __restrict__ W,
-                                                         const float* __restrict__ Aprev, float* __restrict__ dX,
+                                                         const float* Aprev, float* dX,
                                                          int64_t n, int din, int dout) {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= n * din) return;
@@ -546,7 +587,8 @@ __global__ __launch_bounds__(512, CT == 1 && !TRAIN ? 4 : 2) void k_mlp_fused(Ml
 struct GradArgs {
     const float *xn, *acts, *dy, *dz;      // acts, dz: hidden layers after one another
     int n_in, width, depth, splits;
-    int64_t n, rows, P;                    // rows: rows of a split
+    int layer;                             // the one layer of this launch, -1: all
+    int64_t n, rows, P;                    // rows: rows of a split; P: parameters of the launch
     float* grads;                          // splits == 1: written here
     double* part;                          // else: partials [split][P]
 };
@@ -560,14 +602,15 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(GradArgs a) {
     int t = by8 ? (b >> 3) % per : b % per;
     // layers in order: n_in -> width, the hidden ones, width -> 1
     const int W = a.width, tw = (W + kGradTile - 1) / kGradTile, ti = (a.n_in + kGradTile - 1) / kGradTile;
-    int l = 0;
-    if (t >= tw * ti) {
+    int l = a.layer < 0 ? 0 : a.layer;
+    if (a.layer < 0 && t >= tw * ti) {
         t -= tw * ti;
         l = 1 + t / (tw * tw) < a.depth ? 1 + t / (tw * tw) : a.depth;
         t -= (l - 1) * tw * tw;
     }
     const int din = l == 0 ? a.n_in : W, dout = l == a.depth ? 1 : W;
-    const int64_t w_off = l == 0 ? 0 : (int64_t)W * (a.n_in + 1) + (int64_t)(l - 1) * W * (W + 1);
+    const int64_t w_off =
+        l == 0 || a.layer >= 0 ? 0 : (int64_t)W * (a.n_in + 1) + (int64_t)(l - 1) * W * (W + 1);
     const int64_t b_off = w_off + (int64_t)din * dout;
     const int ti_n = l == 0 ? ti : tw;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -655,11 +698,11 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(GradArgs a) {
 }
 
 // Gradient partials added in range order, the Adam update of the same weight
-// (adam != 0), and the loss (the launch's last block).
+// (adam != 0), and the loss (the launch's last block; loss null: none).
 __global__ __launch_bounds__(256) void k_mlp_reduce(const double* part, int splits, int64_t P, float* g, float* p,
                                                     float* m, float* v, int adam, AdamArgs aa, const double* lpart,
                                                     int nb, int64_t n, float* loss) {
-    if (blockIdx.x == gridDim.x - 1) {
+    if (loss && blockIdx.x == gridDim.x - 1) {
         __shared__ double red[256];
         double s = 0;
         for (int i = threadIdx.x; i < nb; i += 256) s += lpart[i];
@@ -685,18 +728,6 @@ __global__ __launch_bounds__(256) void k_mlp_reduce(const double* part, int spli
         gi = g[i];
     }
     if (adam) adam_update(p, gi, m, v, i, aa);
-}
-
-// The fused launch serves networks whose layers a block's eight waves hold in
-// registers (up to 256 columns) and whose rows fit 64 KB of LDS; others go
-// layer by layer.  Rows per block: 64 for the most reuse of a block's weight
-// reads, fewer while that leaves CUs without a block.  Returns the LDS bytes of
-// a block of 16 rt rows, 0 if the shape is not served.
-static size_t fused_lds(const MlpLayout& L, int rt, bool train, int* pitch) {
-    const int cols = (std::max(L.n_in, L.width) + 15) / 16 * 16;
-    *pitch = cols + 4;      // rows start 4 LDS banks apart: conflict-free 16-byte reads
-    const size_t b = (size_t)16 * rt * *pitch * 4 * (train ? L.depth + 1 : 1);
-    return cols <= 256 && b <= 60 * 1024 ? b : 0;
 }
 
 template <int RT, bool TRAIN>
@@ -784,20 +815,6 @@ static void gradients(const MlpLayout& L, float* state, const float* x, const fl
     a.dy = ws + o.dy;
     a.dz = ws + o.dz;
     a.part = lpart;
-    int64_t nb = launch_fused<true>(L, a, s);
-    if (!nb) {
-        forward_layers(L, state, x, n, ws, ws + o.y, s);
-        nb = nblk(n, 256);
-        hipLaunchKernelGGL(k_loss_grad, dim3((unsigned)nb), dim3(256), 0, s, ws + o.y, t, w, a.dy, lpart, n);
-        const float* dz = a.dy;
-        for (int l = L.n_layers - 1; l > 0; --l) {
-            float* below = a.dz + (int64_t)(l - 1) * n * L.width;
-            hipLaunchKernelGGL(k_linear_bwd_data, dim3(nblk(n * L.din[l], 256)), dim3(256), 0, s, dz,
-                               params + L.w_off[l], a.acts + (int64_t)(l - 1) * n * L.width, below, n, L.din[l],
-                               L.dout[l]);
-            dz = below;
-        }
-    }
     GradArgs g{};
     g.xn = a.xn;
     g.acts = a.acts;
@@ -806,17 +823,46 @@ static void gradients(const MlpLayout& L, float* state, const float* x, const fl
     g.n_in = L.n_in;
     g.width = L.width;
     g.depth = L.depth;
-    g.splits = (int)grad_splits(L, n);
     g.n = n;
-    if (g.splits >= 8) g.splits &= ~7;      // as many ranges on each XCD
-    g.rows = (n + g.splits - 1) / g.splits;
-    g.P = L.P;
-    g.grads = state + L.grads_off;
     g.part = (double*)(ws + o.grad);
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)(grad_tiles(L) * g.splits)), dim3(256), 0, s, g);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3(nblk(L.P, 256) + 1), dim3(256), 0, s, g.part, g.splits, L.P, g.grads,
-                       params, state + L.m_off, state + L.v_off, adam ? 1 : 0, adam ? *adam : AdamArgs{}, lpart,
-                       (int)nb, n, loss);
+    int64_t nb = launch_fused<true>(L, a, s);
+    // weight gradients of one layer or (layer < 0) of all
+    auto wgrad = [&](int layer) {
+        g.layer = layer;
+        g.splits = (int)grad_splits(L, n, layer);
+        g.rows = (n + g.splits - 1) / g.splits;
+        g.P = layer < 0 ? L.P : layer_params(L, layer);
+        g.grads = state + L.grads_off + (layer < 0 ? 0 : L.w_off[layer]);
+        hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)(grad_tiles(L, layer) * g.splits)), dim3(256), 0, s, g);
+    };
+    // ... added up, and the update; the loss with the first launch
+    auto reduce = [&](bool with_loss) {
+        const int64_t at = g.grads - state - L.grads_off;
+        hipLaunchKernelGGL(k_mlp_reduce, dim3(nblk(g.P, 256) + (with_loss ? 1 : 0)), dim3(256), 0, s, g.part, g.splits,
+                           g.P, g.grads, params + at, state + L.m_off + at, state + L.v_off + at, adam ? 1 : 0,
+                           adam ? *adam : AdamArgs{}, lpart, (int)nb, n, with_loss ? loss : nullptr);
+    };
+    if (!nb) {
+        const bool in_place = o.dz == o.acts;
+        forward_layers(L, state, x, n, ws, ws + o.y, s);
+        nb = nblk(n, 256);
+        hipLaunchKernelGGL(k_loss_grad, dim3((unsigned)nb), dim3(256), 0, s, ws + o.y, t, w, a.dy, lpart, n);
+        const float* dz = a.dy;
+        for (int l = L.n_layers - 1; l >= 0; --l) {
+            if (in_place) wgrad(l);
+            if (l > 0) {
+                float* below = a.dz + (int64_t)(l - 1) * n * L.width;
+                hipLaunchKernelGGL(k_linear_bwd_data, dim3(nblk(n * L.din[l], 256)), dim3(256), 0, s, dz,
+                                   params + L.w_off[l], a.acts + (int64_t)(l - 1) * n * L.width, below, n, L.din[l],
+                                   L.dout[l]);
+                dz = below;
+            }
+            if (in_place) reduce(l == L.n_layers - 1);
+        }
+        if (in_place) return;
+    }
+    wgrad(-1);
+    reduce(true);
 }
 
 }  // namespace tn
@@ -845,7 +891,7 @@ int tn_mlp_sizes(const tn_mlp_shape* s, int64_t batch, int64_t* n_params, size_t
         MlpLayout L = layout_of(s);
         if (n_params) *n_params = L.P;
         if (state_bytes) *state_bytes = (size_t)L.total * 4;
-        if (ws_bytes) *ws_bytes = (size_t)ws_layout(L, std::max<int64_t>(1, batch)).total * 4;
+        if (ws_bytes) *ws_bytes = (size_t)ws_floats(L, std::max<int64_t>(1, batch)) * 4;
     });
 }
 
