@@ -145,7 +145,9 @@ typedef struct {
                                 the dispatch itself (hipExtLaunchKernelGGL) so they bracket
                                 the kernel and not the queue, accumulated per kernel
                                 (tn_exec_kernel_stats); needs use_graph = 0 (TN_EINVAL
-                                otherwise) */
+                                otherwise).  Every level is then launched by itself:
+                                small consecutive levels, which estimates otherwise
+                                run in one launch, are not joined */
     int32_t no_gather;       /* 1 = always transpose operands into GEMM order instead of
                                 letting MFMA steps read them in stored order */
     int32_t no_group;        /* 1 = one launch per contraction step instead of one grouped
@@ -511,7 +513,8 @@ int tn_plan_describe(tn_plan plan, char* buf, size_t* len);
 
 /* JSON description of a prepared schedule's steps (shapes, instances,
  * modes; with time_kernels, each launch's accumulated duration t_ms over t_n
- * runs) into buf; *len receives the needed size. */
+ * runs; estimate_launches: the kernel launches of one estimate) into buf; *len
+ * receives the needed size. */
 int tn_exec_describe(tn_exec ex, char* buf, size_t* len);
 
 /* The staged constant region of a prepared (or size-queried) schedule: fixed

@@ -1939,7 +1939,7 @@ static void build_schedule(tn_exec_s* ex, int n, const tn_plan* plans, const tn_
                 L.jobs = Ref{R_CONST, ex->cbuf.reserve((int64_t)L.n_jobs * (int64_t)sizeof(GettJob))};
                 L.table = Ref{R_CONST, ex->cbuf.reserve(L.blocks * 4)};
             }
-    if (!ex->opts.time_kernels && !ex->probe)      // timed launches run one by one
+    if (!ex->opts.time_kernels && !ex->probe)      // timed launches run one by one, a level each
         for (auto* list : {&ex->launches_const, &ex->launches, &ex->launches64}) plan_chains(ex, *list);
     for (const PlanExec& pe : ex->plans) {
         ex->tail_blocks += (pe.n_terms + 255) / 256;
@@ -2382,13 +2382,23 @@ static void autotune(tn_exec_s* ex) {
     HIPCHK(hipStreamSynchronize(s));
 }
 
+// Kernel launches of one estimate: joined levels are one, the tail one or two.
+static int64_t estimate_launches(const tn_exec_s* ex) {
+    int64_t n = ex->plans.empty() ? 0 : tail_launches(ex->tail_most);
+    n += (int64_t)ex->plain_launches.size() * ex->plain_terms;
+    for (auto* list : {&ex->launches, &ex->launches64})
+        for (const Launch& L : *list) n += L.kind == L_GROUP ? L.blocks > 0 && (L.chain < 0 || L.chain_head) : 1;
+    return n;
+}
+
 static std::string describe_exec(const tn_exec_s* ex) {
     std::ostringstream os;
     os.precision(17);
     os << "{\"const_bytes\":" << ex->const_bytes << ",\"work_bytes\":" << ex->work_bytes
        << ",\"work1_bytes\":" << ex->work1_bytes
        << ",\"mode\":" << ex->opts.mode << ",\"plain_terms\":" << ex->plain_terms
-       << ",\"tail_blocks\":" << ex->tail_blocks << ",\"tuning\":[";
+       << ",\"tail_blocks\":" << ex->tail_blocks << ",\"estimate_launches\":" << estimate_launches(ex)
+       << ",\"tuning\":[";
     {
         bool f1 = true;
         for (auto& kv : ex->tuning) {

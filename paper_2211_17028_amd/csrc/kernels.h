@@ -216,6 +216,8 @@ struct TailJob {
     int64_t block0;                // first block of this circuit in the term launch
     int32_t n_levels, pad_;
 };
+// launches of the tail of circuits of up to most_blocks blocks of terms
+int tail_launches(int64_t most_blocks);
 // d_part: blocks x (TN_MAX_LEVEL + 1) (sum, comp) pairs of scratch; the level
 // sums and the FP32 diagnostic value go res_shift bytes past the addresses in
 // the jobs (a results slot of a submitted estimate).  most_blocks: of one job.

@@ -2190,6 +2190,7 @@ const char* kernel_name(int id) {
     case K_TILED64: return "k_gemm_tiled_c128";
     case K_PERM32: return "k_permute<float2>";
     case K_PERM64: return "k_permute<double2>";
+    // k_gett_group by the precision of a launch's jobs (one kernel serves all)
     case K_GROUP32: return "k_gett_group<float>";
     case K_GROUP64: return "k_gett_group<double>";
     case K_GROUPMIX: return "k_gett_group<mixed>";
@@ -2333,10 +2334,12 @@ void launch_level_sum(const double* x, const int64_t* starts, int n_levels, doub
     hipLaunchKernelGGL(k_level_sum, dim3(n_levels), dim3(256), 0, s, x, starts, out);
 }
 
+int tail_launches(int64_t most_blocks) { return most_blocks <= kTailSmallBlocks ? 1 : 2; }
+
 void launch_tail(const TailJob* d_jobs, int n_jobs, int64_t blocks, int64_t most_blocks, int max_levels,
                  double* d_part, int64_t res_shift, hipStream_t s) {
     if (n_jobs == 0) return;
-    if (most_blocks <= kTailSmallBlocks) {
+    if (tail_launches(most_blocks) == 1) {
         hipLaunchKernelGGL(k_tail_small, dim3((unsigned)n_jobs), dim3(1024), 0, s, d_jobs, res_shift);
         return;
     }
