@@ -342,8 +342,10 @@ constexpr int kSplitDefaultMax = 16;
 // the small kernel's block per output would stream a whole row and column of
 // the operands per output.  From 2^17 terms and 64 outputs on also where slices
 // fill only part of a tile (8 x 16 outputs over 2^21 terms, twice: 1306 us on the
-// small kernel, 924 us split; 8 x 16 over 2^17 40 us less; at 2^14 and 2^15 terms
-// 8 x 16 outputs took 7 to 15 us more, 32 x 16 6 us less).
+// small kernel, 924 us split; 8 x 16 over 2^17 40 us less).  The line is that of
+// the emptiest tiles: at 2^14 and 2^15 terms 8 x 16 outputs took 7 to 15 us more
+// split, while 32 x 16 ones, which fill half a tile, took 6 us less at 2^14; how
+// full a tile is does not enter the rule.
 constexpr int kSplitLongMax = 512;
 // A matrix-core job with at most this share of the flops of its level's main
 // tile shape takes that shape, so that it runs in the main launch.
@@ -654,13 +656,15 @@ struct Builder {
                        int64_t ninst, int64_t nbatch, PosIn posin, ByPos by_pos, SliceVec slice_vec, int fp64) {
         // FP64 steps run on the 64 x 64 or 32 x 32 FMA tiles (tile ids 1 and 4's shapes)
         const int64_t esz = fp64 ? 16 : 8;
-        // A tile's rate in a level, relative (order of the tile ids).  128 x 32 leads:
-        // full launches of it reach 93 to 98 % of the 128 x 64 tile's rate (86.8
-        // against 88.3 TFLOP/s over 256 terms), in half the work per tile, so a
-        // level's last round over the CUs is shorter.  Its entry was 0.75 when its
-        // waves held 64 rows; from there to 1, with 0.95 for 128 x 64: twelve packed
-        // circuits 2046 -> 1718 us, a range of 25-qubit amplitudes 1074 -> 1036,
-        // 25-qubit grid 1115 -> 1099, 36-qubit QAOA the same.
+        // Weights of the tile shapes (order of the tile ids): fitted to whole estimates,
+        // not their rates.  (In full launches the 64-row tiles reach 0.88 to 1.02 of the
+        // 128 x 64 tile's rate, 128 x 32 0.93 to 0.98; what the weights stand for beside
+        // the rate is how short a level's last round over the CUs is and how many tiles
+        // its reduction and setup have.)  128 x 32 was 0.75 and 128 x 64 1.0 before
+        // 128 x 32 took 32-row waves; chosen among six tables on twelve packed circuits
+        // (2038 -> 1710 us), a range of 25-qubit amplitudes (1061 -> 1043), a 25-qubit grid
+        // (1115 -> 1099) and a 36-qubit QAOA (the same).  Ten circuits drawn from the same
+        // families afterwards: 1.00 to 1.09 times as fast, none slower.
         static const double kEffWide[K_MFMA_TILES] = {0.95, 0.6, 1.0, 0.5, 0.35, 0.45, 0.3, 0.2};
         // for a small workspace (build_fitting): 128 x 32 is taken less often, whose
         // split sums need more scratch than the smaller tiles'
@@ -1631,11 +1635,14 @@ static void merge_fp64_chain(tn_exec_s* ex) {
 // block per independent part (k_gett_chain).  A launch joins while every part's
 // blocks of its level, four at a time, take no longer than a launch of its own:
 // about 1.2 us per round plus 0.6 us per batch of loads of its longest sum,
-// against 3.5 us more for a launch than for a round (8-qubit chain, 3 levels of
-// 1 to 6 blocks and the tail: 37.4 us an estimate as 5 launches, 29.6 as 2).
+// against 3.5 us more for a launch than for a round: 8 blocks of short sums, 4
+// of longer ones.  Its jobs can join parts of earlier levels, which may then
+// have up to 12 blocks at a level (a third round, still about the launch that
+// it saves).  (8-qubit chain, 3 levels of 1 to 6 blocks and the tail: 37.4 us an
+// estimate as 5 launches, 29.6 as 2.)
 static void plan_chains(tn_exec_s* ex, std::vector<Launch>& list) {
     constexpr size_t kMaxJobs = 400;
-    constexpr int kMaxBlocks = 12;                     // of a part at one level
+    constexpr int kMaxBlocks = 12;                     // of a part at an earlier level
     struct Span {
         int64_t a0, a1, b0, b1, c0, c1;                // bytes read (a, b) and written (c), regions apart
     };
@@ -1666,7 +1673,7 @@ static void plan_chains(tn_exec_s* ex, std::vector<Launch>& list) {
                 batches = std::max(batches, k / (g.split == 1 ? (g.fp64 ? 8 : 16) : (g.fp64 ? 4 : 8)));
             }
             const double t = 1.2 + 0.6 * batches;
-            const int64_t most = std::min<int64_t>(kMaxBlocks, 4 * (int64_t)(1.0 + 3.5 / t));
+            const int64_t most = 4 * (int64_t)(1.0 + 3.5 / t);
             bool ok = true;
             for (const GroupJob& g : L.hjobs) ok = ok && g.rl == 0 && g.cl == 0 && job_blocks(g) <= most;
             if (!ok) break;
@@ -2613,6 +2620,8 @@ static void issue_estimate(tn_exec_s* ex, hipStream_t s) {
     }
 }
 
+// One circuit's result from its level sums ((sum, comp) pairs, u = 0..level):
+// A(u) as the compensated running sum, and the truncation bound of the split.
 static void fill_one(const Plan& P, const Terms& T, int64_t n_live, int64_t n_zero, const double* sums,
                      double x0_fp32, tn_result& r) {
     std::memset(&r, 0, sizeof(r));
