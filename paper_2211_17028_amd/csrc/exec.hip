@@ -658,18 +658,26 @@ struct Builder {
         const int64_t esz = fp64 ? 16 : 8;
         // Weights of the tile shapes (order of the tile ids): fitted to whole estimates,
         // not their rates.  (In full launches the 64-row tiles reach 0.88 to 1.02 of the
-        // 128 x 64 tile's rate, 128 x 32 0.93 to 0.98; what the weights stand for beside
-        // the rate is how short a level's last round over the CUs is and how many tiles
-        // its reduction and setup have.)  128 x 32 was 0.75 and 128 x 64 1.0 before
-        // 128 x 32 took 32-row waves; chosen among six tables on twelve packed circuits
-        // (2038 -> 1710 us), a range of 25-qubit amplitudes (1061 -> 1043), a 25-qubit grid
-        // (1115 -> 1099) and a 36-qubit QAOA (the same).  Ten circuits drawn from the same
-        // families afterwards: 1.00 to 1.09 times as fast, none slower.
-        static const double kEffWide[K_MFMA_TILES] = {0.95, 0.6, 1.0, 0.5, 0.35, 0.45, 0.3, 0.2};
+        // 128 x 64 tile's rate, 128 x 32 0.93 to 0.98, the 16-wide ones 0.53 to 0.76; what
+        // the weights stand for beside the rate is how short a level's last round over the
+        // CUs is, how many tiles its setup and reduction have and, for packed circuits,
+        // that each further shape in a level is one more launch.)  kEffNarrow is from
+        // before 128 x 32 had 32-row waves.  Packed circuits: twelve 2020 us with it, 1689
+        // with kEffPacked; of 15 drawn sets 12 are 7 to 35 % faster, three of 7 to 17 ms 1
+        // to 2 % slower.  One circuit alone: with kEffPacked a 36-qubit QAOA's 8208 slices
+        // of 8 x 16 outputs over 1024 terms run half padded on 128 x 32 (376 us; 261 on 32
+        // x 16), the estimate takes 920 us, 815 with kEffNarrow, 812 with kEffOne (25-qubit
+        // grid 1092 -> 1064, a range of amplitudes 985 -> 882), which has the 16-wide tiles
+        // higher.  kEffOne was chosen on 48 drawn circuits; on 26 others it is 2.9 % faster
+        // than kEffNarrow and 0.6 % than kEffPacked in the mean, at most 2 % slower than
+        // either.  The rates of full launches as weights: the amplitudes 1213 us, the
+        // packed circuits 1974.
+        static const double kEffPacked[K_MFMA_TILES] = {0.95, 0.6, 1.0, 0.5, 0.35, 0.45, 0.3, 0.2};
+        static const double kEffOne[K_MFMA_TILES] = {0.95, 0.6, 1.0, 0.5, 0.35, 0.5, 0.35, 0.27};
         // for a small workspace (build_fitting): 128 x 32 is taken less often, whose
         // split sums need more scratch than the smaller tiles'
         static const double kEffNarrow[K_MFMA_TILES] = {1.0, 0.6, 0.75, 0.5, 0.35, 0.45, 0.3, 0.2};
-        const double* kEff = narrow ? kEffNarrow : kEffWide;
+        const double* kEff = narrow ? kEffNarrow : quantize_tiles ? kEffOne : kEffPacked;
         static const double kEff64[K_MFMA_TILES] = {0, 1.0, 0, 0, 0.7, 0, 0, 0};
         const int rk = (int)K.size();
         const int64_t ns = ninst * nbatch;
