@@ -268,8 +268,8 @@ int tn_terms_get(tn_terms terms, int8_t* patterns, double* weights);
  *   d_ws (the caller keeps d_ws alive and unmodified until tn_exec_destroy).
  *   Below the size that the query reports, a schedule with less scratch for
  *   split sums is tried before TN_ENOMEM; *need_bytes receives the size of the
- *   schedule that is bound.  tn_estimate (before it goes to term ranges, and in
- *   each of them), tn_contract_batch and tn_estimate_noalloc do the same.
+ *   schedule that is bound.  tn_estimate (before it goes to term ranges, and where
+ *   one term is left), tn_contract_batch and tn_estimate_noalloc do the same.
  *   Its sums are grouped otherwise, so values agree to rounding.
  *   With opts->tune = 1 the query reports the largest workspace of the
  *   schedules the autotuner times; a smaller d_ws that still holds the untuned

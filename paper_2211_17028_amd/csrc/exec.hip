@@ -249,6 +249,7 @@ struct tn_exec_s {
     std::vector<tn::Chain> chains;
     bool probe = false;                     // built for its shapes only (see build_exec)
     bool narrow = false;                    // split sums with less scratch (see build_fitting)
+    int64_t bare_bytes = 0;                 // without tile lists and scratch: no tile choice needs less
     // packed circuits: the tail runs as one finalize and one level-sum launch
     // the tail of all packed circuits: one record per circuit, the per-block
     // level partials of the term launch
@@ -347,6 +348,7 @@ constexpr int kSplitDefaultMax = 16;
 // split, while 32 x 16 ones, which fill half a tile, took 6 us less at 2^14; how
 // full a tile is does not enter the rule.
 constexpr int kSplitLongMax = 512;
+constexpr int kSplitLongLog = 17;
 // A matrix-core job with at most this share of the flops of its level's main
 // tile shape takes that shape, so that it runs in the main launch.
 constexpr double kSmallJobShare = 0.25;
@@ -542,6 +544,8 @@ struct Builder {
     tn_exec_s* ex;
     Arena work;                // FP32 batch (main stream)
     Arena work2;               // FP64 dominant-term pass (side stream, runs concurrently)
+    Arena bare, bare2;         // the same without scratch (a bound for build_fitting)
+    std::vector<int64_t> bare_off;
     bool grouping = true;      // small steps of one tree level share one launch
     // Slot-free intermediates (no noise slot below them) are the same for every
     // term and every estimate: with fold_const their steps go to const32 /
@@ -1200,7 +1204,7 @@ struct Builder {
             // their shape would fill a tile: a launch of their own costs more
             const bool long_sum = fp64 && rk > 8 && step_flops >= kMfmaMinFlops &&
                                   (std::min(FA.size(), FB.size()) >= 5 ||
-                                   (!ksplit_user && !narrow && rk >= 17 && FA.size() + FB.size() >= 6));
+                                   (!ksplit_user && !narrow && rk >= kSplitLongLog && FA.size() + FB.size() >= 6));
             bool to_tile = (big && step_flops >= kTileMinFlops) || heavy || long_sum;
             if (!fp64 && small_levels && small_levels->count(st.level)) to_tile = false;
             // inner sums under 8 terms would fill less than one staged chunk of a
@@ -1459,7 +1463,8 @@ struct Builder {
     // steps; buffers are released after the level.  Otherwise the steps run one
     // by one in the given order, each releasing its operands.
     void emit(std::vector<StepRec>& steps, int fp64, bool by_level, std::vector<Launch>* out) {
-        Arena& wk = fp64 ? work2 : work;
+        Arena &wk = fp64 ? work2 : work, &bk = fp64 ? bare2 : bare;
+        bare_off.resize(node_ref.size());
         const int wreg = fp64 ? R_WORK2 : R_WORK;
         auto subst = [&](Ref& r) {
             if (r.region == R_NODE) r = node_ref[r.off];
@@ -1481,6 +1486,7 @@ struct Builder {
             for (int i : grp) {
                 StepRec& st = steps[i];
                 node_ref[st.c_node] = st.has_fixed ? st.c_fixed : Ref{wreg, wk.alloc(st.c_bytes)};
+                if (!st.has_fixed) bare_off[st.c_node] = bk.alloc(st.c_bytes);
                 for (size_t q = 0; q < st.temp_ids.size(); ++q)
                     temp_ref[st.temp_ids[q]] = Ref{wreg, wk.alloc(st.temp_bytes[q])};
             }
@@ -1579,7 +1585,10 @@ struct Builder {
                 for (size_t q = 0; q < st.temp_ids.size(); ++q)
                     wk.release(temp_ref[st.temp_ids[q]].off, st.temp_bytes[q]);
                 for (int nd : {st.a_node, st.b_node})
-                    if (!node_leaf[nd] && node_ref[nd].region == wreg) wk.release(node_ref[nd].off, node_bytes[nd]);
+                    if (!node_leaf[nd] && node_ref[nd].region == wreg) {
+                        wk.release(node_ref[nd].off, node_bytes[nd]);
+                        bk.release(bare_off[nd], node_bytes[nd]);
+                    }
             }
         }
     }
@@ -1968,6 +1977,10 @@ static void build_schedule(tn_exec_s* ex, int n, const tn_plan* plans, const tn_
     ex->const_bytes = ex->cbuf.region_bytes();
     ex->work1_bytes = round_up(bw.work.peak, 256);
     ex->work_bytes = ex->work1_bytes + round_up(bw.work2.peak, 256);
+    ex->bare_bytes = ex->const_bytes + bw.bare.peak + bw.bare2.peak;
+    for (auto* list : {&ex->launches_const, &ex->launches, &ex->launches64})
+        for (const Launch& L : *list)
+            if (L.kind == L_MGROUP) ex->bare_bytes -= L.n_tiles * (int64_t)sizeof(MfmaTile);
 }
 
 static void* resolve(tn_exec_s* ex, const Ref& r) {
@@ -2767,10 +2780,17 @@ static std::unique_ptr<tn_exec_s> build_fitting(int n, const tn_plan* plans, con
                                                 const tn_exec_opts* opts, TermRange range, size_t avail,
                                                 size_t (*need)(const tn_exec_s*) = exec_need) {
     std::unique_ptr<tn_exec_s> ex = build_exec(n, plans, terms, opts, range);
-    bool tiles = false;                        // without tile jobs both are the same
+    if (need(ex.get()) <= avail) return ex;
+    // Not where both are the same (no FP32 tiles, no split FP64 sums of part-filled
+    // tiles), where what a tile choice changes (scratch, tile lists) is too little
+    // of the size, or where the rest is already above `avail` (0: the smallest;
+    // released buffers are reused in another order, hence the hundredth).
+    bool differ = false;
     for (auto* list : {&ex->launches_const, &ex->launches, &ex->launches64})
-        for (const Launch& L : *list) tiles = tiles || L.kind == L_MGROUP;
-    if (need(ex.get()) <= avail || !tiles) return ex;
+        for (const Launch& L : *list)
+            for (const MJob& j : L.mjobs) differ = differ || !L.fp64 || j.k_log >= kSplitLongLog;
+    const double whole = (double)need(ex.get()), bare = 0.99 * (double)ex->bare_bytes;
+    if (!differ || (avail ? (double)avail < bare : whole < 1.02 * bare)) return ex;
     std::unique_ptr<tn_exec_s> small = build_exec(n, plans, terms, opts, range, true);
     return need(small.get()) < need(ex.get()) ? std::move(small) : std::move(ex);
 }
@@ -3122,21 +3142,26 @@ static int64_t chunk_acc_bytes(const Terms& T) {
 // single-term schedule other than the all-dominant term's has the same path
 // with one instance per node, so the first live term after term 0 stands for
 // them all; term 0's range holds the FP64 pass.
-static size_t min_workspace(int n, const tn_plan* plans, const tn_terms* terms) {
+// (avail: a size up to which the exact minimum does not matter)
+static size_t min_workspace(int n, const tn_plan* plans, const tn_terms* terms, size_t avail = 0) {
     if (n < 1 || !plans || !terms) fail(TN_EINVAL, "need at least one plan with its terms");
     size_t mx = 0;
     for (int i = 0; i < n; ++i) {
         if (!plans[i] || !terms[i]) fail(TN_EINVAL, "null plan or term handle");
         const Terms& T = *reinterpret_cast<const Terms*>(terms[i]);
         size_t m = 0;
-        if (T.n > 0) m = exec_need(build_fitting(1, &plans[i], &terms[i], &estimate_opts(), TermRange{0, 1}, 0).get());
+        const size_t acc = (size_t)chunk_acc_bytes(T), room = avail > acc ? avail - acc : 0;
+        auto one = [&](int64_t t) {
+            m = std::max(m, exec_need(build_fitting(1, &plans[i], &terms[i], &estimate_opts(), TermRange{t, t + 1},
+                                                    room).get()));
+        };
+        if (T.n > 0) one(0);
         for (int64_t t = 1; t < T.n; ++t)
             if (!T.zero[t] && !T.pruned[t]) {
-                m = std::max(m, exec_need(build_fitting(1, &plans[i], &terms[i], &estimate_opts(),
-                                                        TermRange{t, t + 1}, 0).get()));
+                one(t);
                 break;
             }
-        mx = std::max(mx, (size_t)chunk_acc_bytes(T) + m);
+        mx = std::max(mx, acc + m);
     }
     return mx;
 }
@@ -3156,13 +3181,17 @@ static void estimate_chunked(int n, const tn_plan* plans, const tn_terms* terms,
         const std::vector<int64_t> starts = level_starts(T);
         HIPCHK(hipMemcpyAsync(d_starts, starts.data(), starts.size() * 8, hipMemcpyHostToDevice, s));
         int64_t n_live = 0, n_zero = 0;
-        int64_t lo = 0, cnt = T.n;
+        int64_t lo = 0, cnt = n == 1 ? (T.n + 1) / 2 : T.n;     // (one circuit as a whole did not fit)
         while (lo < T.n) {
             cnt = std::min(cnt, T.n - lo);
             std::unique_ptr<tn_exec_s> ex;
             for (;;) {
-                ex = build_fitting(1, &plans[i], &terms[i], &estimate_opts(), TermRange{lo, lo + cnt}, avail);
+                ex = build_exec(1, &plans[i], &terms[i], &estimate_opts(), TermRange{lo, lo + cnt});
                 if (exec_need(ex.get()) <= avail) break;
+                if (cnt == 1) {
+                    ex = build_fitting(1, &plans[i], &terms[i], &estimate_opts(), TermRange{lo, lo + 1}, avail);
+                    if (exec_need(ex.get()) <= avail) break;
+                }
                 if (cnt == 1) fail(TN_ENOMEM, "one term's schedule does not fit the workspace");
                 cnt = (cnt + 1) / 2;
             }
@@ -3650,7 +3679,7 @@ int tn_estimate(int32_t n, const tn_plan* plans, const tn_terms* terms, void* d_
             std::unique_ptr<tn_exec_s> ex = build_fitting(n, plans, terms, &estimate_opts(), TermRange{}, ws_bytes);
             if (exec_need(ex.get()) > ws_bytes) {
                 // below the one-schedule size: term ranges one after another
-                const size_t mn = min_workspace(n, plans, terms);
+                const size_t mn = min_workspace(n, plans, terms, ws_bytes);
                 if (ws_bytes < mn) {
                     std::ostringstream os;
                     os << "workspace too small: " << ws_bytes << " < " << mn
