@@ -25,7 +25,7 @@
  *   tree level.  Job j: slices s < n_slices with C_s = A_s B_s; the element
  *   (row r, inner p) of slice s of A sits at oa[s] + sum_i bit_i(r) << a_row[i]
  *   + sum_i bit_i(p) << a_k[i] (B likewise with ob, b_k, b_col); C_s is an
- *   m x n row-major block at oc[s].  merge = 1: a tile's columns hold `cnt`
+ *   m x n row-major block at oc[s] (offsets >= 0).  merge = 1: a tile's columns hold `cnt`
  *   consecutive slices sharing A; 2: its rows hold `cnt` slices sharing B;
  *   0: one slice per tile (origin tm0, tn0).  Jobs and tiles are device
  *   arrays in the tn_mfma_job / tn_mfma_tile layouts; `tile` selects the tile
