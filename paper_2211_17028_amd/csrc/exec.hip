@@ -1648,118 +1648,147 @@ static void merge_fp64_chain(tn_exec_s* ex) {
     ex->launches64.clear();
 }
 
-// Runs of consecutive grouped launches whose levels are small enough for one
-// block per independent part (k_gett_chain).  A launch joins while every part's
-// blocks of its level, four at a time, take no longer than a launch of its own:
-// about 1.2 us per round plus 0.6 us per batch of loads of its longest sum,
-// against 3.5 us more for a launch than for a round: 8 blocks of short sums, 4
-// of longer ones.  Its jobs can join parts of earlier levels, which may then
-// have up to 12 blocks at a level (a third round, still about the launch that
-// it saves).  (8-qubit chain, 3 levels of 1 to 6 blocks and the tail: 37.4 us an
-// estimate as 5 launches, 29.6 as 2.)
+// Consecutive grouped launches that run as one (k_gett_chain): a list is cut where
+// its time is least, by this model.  A launch by itself takes kChainLaunch plus a
+// round: its blocks run side by side.  A chain takes kChainLaunch plus its longest
+// part: four blocks of a level at a time, one level's rounds after another's, at
+// most kChainBlocks blocks of a level.  (A round is a chain of dependent loads:
+// kChainRound plus kChainBatch per batch of loads of the level's longest sum; in a
+// list that is repeated about 1.2 us instead of 2.5, with the same cuts nearly
+// everywhere.)  8-qubit chain, 3 levels and the tail: 37.4 us an estimate as 5
+// launches, 29.6 as 2.  One-call estimates, whose records come from memory each
+// time: 114 to 185 us where joining up to 8 blocks of every level took 119 to 206
+// (20- to 68-qubit chains and grids, 12 of 14; the others the same).  32 blocks of
+// a level beside a longer part: 240 us instead of 220, hence the limit.
+constexpr double kChainLaunch = 3.5, kChainRound = 2.5, kChainBatch = 0.6;   // us
+constexpr int kChainBlocks = 24;
+
 static void plan_chains(tn_exec_s* ex, std::vector<Launch>& list) {
     constexpr size_t kMaxJobs = 400;
-    constexpr int kMaxBlocks = 12;                     // of a part at an earlier level
-    struct Span {
+    struct Job {
+        const GroupJob* g;
+        int launch, job, blocks;
         int64_t a0, a1, b0, b1, c0, c1;                // bytes read (a, b) and written (c), regions apart
+        std::vector<int> tied;                         // earlier jobs it may not run beside
     };
     auto at = [](const Ref& r) { return r.off + ((int64_t)r.region << 57); };
-    std::vector<const GroupJob*> jobs;
-    std::vector<Span> span;
-    std::vector<int> parent, launch_of, job_of, was;
-    std::vector<std::array<int16_t, kChainLevels>> cnt, cnt_was;   // of a part's root: blocks per level
+    auto joinable = [&](const Launch& L) {
+        if (L.kind != L_GROUP || L.hjobs.size() > kMaxJobs) return false;
+        for (const GroupJob& g : L.hjobs)
+            if (g.rl || g.cl || job_blocks(g) > kChainBlocks) return false;
+        return true;
+    };
+    std::vector<Job> jobs;
+    std::vector<double> round;                         // per launch of the run
+    std::vector<int> first, parent;                    // first job of a launch; parts as a forest over the jobs
+    std::vector<std::array<int16_t, kChainLevels>> blocks;   // of a part's root: per level
+    std::vector<double> part_t;                        // of a part's root
     auto find = [&](int x) {
         while (parent[x] != x) x = parent[x] = parent[parent[x]];
         return x;
     };
-    for (size_t i = 0; i < list.size();) {
-        jobs.clear();
-        span.clear();
-        parent.clear();
-        launch_of.clear();
-        job_of.clear();
-        cnt.clear();
-        size_t j = i;
-        for (; j < list.size() && list[j].kind == L_GROUP && j - i < (size_t)kChainLevels; ++j) {
-            const Launch& L = list[j];
-            if (jobs.size() + L.hjobs.size() > kMaxJobs) break;
-            const int lv = (int)(j - i);
-            double batches = 1;
-            for (const GroupJob& g : L.hjobs) {
-                const double k = std::ldexp(1.0, g.k_log) / (g.split == 1 ? 256 : g.split == 2 ? 4 : 1);
-                batches = std::max(batches, k / (g.split == 1 ? (g.fp64 ? 8 : 16) : (g.fp64 ? 4 : 8)));
-            }
-            const double t = 1.2 + 0.6 * batches;
-            const int64_t most = 4 * (int64_t)(1.0 + 3.5 / t);
-            bool ok = true;
-            for (const GroupJob& g : L.hjobs) ok = ok && g.rl == 0 && g.cl == 0 && job_blocks(g) <= most;
-            if (!ok) break;
-            const size_t n0 = jobs.size();
-            was = parent;
-            cnt_was = cnt;
-            for (size_t q = 0; q < L.hjobs.size(); ++q) {
-                const GroupJob& g = L.hjobs[q];
-                jobs.push_back(&g);
-                span.push_back({at(g.a), at(g.a) + g.a_len, at(g.b), at(g.b) + g.b_len, at(g.c), at(g.c) + g.c_len});
-                parent.push_back((int)parent.size());
-                launch_of.push_back((int)j);
-                job_of.push_back((int)q);
-                cnt.push_back({});
-                cnt.back()[lv] = (int16_t)job_blocks(g);
-            }
-            for (size_t x = n0; x < jobs.size() && ok; ++x)
-                for (size_t y = 0; y < n0; ++y) {
-                    const Span &p = span[x], &q = span[y];
-                    if (!((p.c0 < q.c1 && q.c0 < p.c1) || (p.c0 < q.a1 && q.a0 < p.c1) || (p.c0 < q.b1 && q.b0 < p.c1) ||
-                          (q.c0 < p.a1 && p.a0 < q.c1) || (q.c0 < p.b1 && p.b0 < q.c1)))
-                        continue;
-                    const int u = find((int)x), v = find((int)y);
-                    if (u == v) continue;
-                    parent[u] = v;
-                    for (int l = 0; l <= lv; ++l) {
-                        cnt[v][l] = (int16_t)(cnt[v][l] + cnt[u][l]);
-                        ok = ok && cnt[v][l] <= (l == lv ? most : kMaxBlocks);
-                    }
-                }
-            if (!ok) {
-                jobs.resize(n0);
-                span.resize(n0);
-                launch_of.resize(n0);
-                job_of.resize(n0);
-                parent = was;
-                cnt = cnt_was;
-                break;
-            }
-        }
-        if (j < i + 2) {
-            i = std::max(j, i + 1);
+    for (size_t r0 = 0; r0 < list.size();) {
+        if (!joinable(list[r0])) {
+            ++r0;
             continue;
         }
-        Chain ch;
-        std::map<int, std::vector<int>> part;          // root -> jobs, in level order
-        for (size_t a = 0; a < jobs.size(); ++a) part[find((int)a)].push_back((int)a);
-        std::vector<GettChainPart> parts;
-        for (auto& kv : part) {
-            GettChainPart p{};
-            int lv = -1;
-            for (int a : kv.second) {
-                if (launch_of[a] != lv) p.start[p.n_levels++] = (int)ch.hblocks.size();
-                lv = launch_of[a];
-                if (jobs[a]->split) p.split_levels |= 1u << (p.n_levels - 1);
-                const int64_t nb = job_blocks(*jobs[a]);
-                for (int64_t b = 0; b < nb; ++b) ch.hblocks.push_back({nullptr, launch_of[a], job_of[a], b});
+        jobs.clear();
+        round.clear();
+        first.assign(1, 0);
+        size_t r1 = r0;
+        for (; r1 < list.size() && joinable(list[r1]); ++r1) {
+            const Launch& L = list[r1];
+            double batches = 1;
+            for (size_t q = 0; q < L.hjobs.size(); ++q) {
+                const GroupJob& g = L.hjobs[q];
+                const double k = std::ldexp(1.0, g.k_log) / (g.split == 1 ? 256 : g.split == 2 ? 4 : 1);
+                batches = std::max(batches, k / (g.split == 1 ? (g.fp64 ? 8 : 16) : (g.fp64 ? 4 : 8)));
+                Job p{&g, (int)r1, (int)q, (int)job_blocks(g), at(g.a), at(g.a) + g.a_len, at(g.b), at(g.b) + g.b_len,
+                      at(g.c), at(g.c) + g.c_len, {}};
+                const int from = first[std::max(0, (int)(r1 - r0) - kChainLevels + 1)];
+                for (int y = from; y < first.back(); ++y) {
+                    const Job& e = jobs[y];
+                    if ((p.c0 < e.c1 && e.c0 < p.c1) || (p.c0 < e.a1 && e.a0 < p.c1) || (p.c0 < e.b1 && e.b0 < p.c1) ||
+                        (e.c0 < p.a1 && p.a0 < e.c1) || (e.c0 < p.b1 && p.b0 < e.c1))
+                        p.tied.push_back(y);
+                }
+                jobs.push_back(std::move(p));
             }
-            p.start[p.n_levels] = (int)ch.hblocks.size();
-            parts.push_back(p);
+            first.push_back((int)jobs.size());
+            round.push_back(kChainRound + kChainBatch * batches);
         }
-        ch.n_parts = (int)parts.size();
-        ch.parts = Ref{R_CONST, ex->cbuf.add(parts.data(), (int64_t)(parts.size() * sizeof(GettChainPart)))};
-        ch.blocks = Ref{R_CONST, ex->cbuf.reserve((int64_t)(ch.hblocks.size() * sizeof(GettChainBlock)))};
-        for (auto& b : ch.hblocks) b.launch = &list[b.launch_index];
-        for (size_t q = i; q < j; ++q) list[q].chain = (int)ex->chains.size();
-        list[i].chain_head = true;
-        ex->chains.push_back(std::move(ch));
-        i = j;
+        const int n = (int)(r1 - r0);
+        parent.resize(jobs.size());
+        blocks.resize(jobs.size());
+        part_t.resize(jobs.size());
+        // adds launch i + lv to the parts of launches i ... i + lv - 1; returns the longest part
+        auto add = [&](int i, int lv, double longest) {
+            auto rounds = [](int b) { return (b + 3) / 4; };
+            for (int x = first[i + lv]; x < first[i + lv + 1]; ++x) {
+                parent[x] = x;
+                blocks[x] = {};
+                blocks[x][lv] = (int16_t)jobs[x].blocks;
+                part_t[x] = round[i + lv] * rounds(jobs[x].blocks);
+                for (int y : jobs[x].tied) {
+                    if (y < first[i]) continue;
+                    const int u = find(x), v = find(y);
+                    if (u == v) continue;
+                    parent[u] = v;
+                    part_t[v] = 0;
+                    for (int l = 0; l <= lv; ++l) {
+                        blocks[v][l] = (int16_t)(blocks[v][l] + blocks[u][l]);
+                        part_t[v] += blocks[v][l] > kChainBlocks ? 1e300 : round[i + l] * rounds(blocks[v][l]);
+                    }
+                }
+                longest = std::max(longest, part_t[find(x)]);
+            }
+            return longest;
+        };
+        std::vector<double> best(n + 1, 1e300);        // time of the run's first launches
+        std::vector<int> cut(n + 1, 0);
+        best[0] = 0;
+        for (int i = 0; i < n; ++i) {
+            double longest = 0;
+            for (int lv = 0; lv < kChainLevels && i + lv < n && first[i + lv + 1] - first[i] <= (int)kMaxJobs; ++lv) {
+                longest = add(i, lv, longest);
+                const double t = best[i] + kChainLaunch + (lv == 0 ? round[i] : longest);
+                if (t < best[i + lv + 1]) {
+                    best[i + lv + 1] = t;
+                    cut[i + lv + 1] = i;
+                }
+            }
+        }
+        std::vector<std::pair<int, int>> chains;       // [from, to)
+        for (int e = n; e > 0; e = cut[e])
+            if (e - cut[e] > 1) chains.push_back({cut[e], e});
+        for (auto c = chains.rbegin(); c != chains.rend(); ++c) {
+            for (int lv = 0; c->first + lv < c->second; ++lv) add(c->first, lv, 0);
+            Chain ch;
+            std::map<int, std::vector<int>> part;      // root -> jobs, in level order
+            for (int x = first[c->first]; x < first[c->second]; ++x) part[find(x)].push_back(x);
+            std::vector<GettChainPart> parts;
+            for (auto& kv : part) {
+                GettChainPart p{};
+                int launch = -1;
+                for (int x : kv.second) {
+                    const Job& b = jobs[x];
+                    if (b.launch != launch) p.start[p.n_levels++] = (int)ch.hblocks.size();
+                    launch = b.launch;
+                    if (b.g->split) p.split_levels |= 1u << (p.n_levels - 1);
+                    for (int64_t q = 0; q < b.blocks; ++q) ch.hblocks.push_back({nullptr, b.launch, b.job, q});
+                }
+                p.start[p.n_levels] = (int)ch.hblocks.size();
+                parts.push_back(p);
+            }
+            ch.n_parts = (int)parts.size();
+            ch.parts = Ref{R_CONST, ex->cbuf.add(parts.data(), (int64_t)(parts.size() * sizeof(GettChainPart)))};
+            ch.blocks = Ref{R_CONST, ex->cbuf.reserve((int64_t)(ch.hblocks.size() * sizeof(GettChainBlock)))};
+            for (auto& b : ch.hblocks) b.launch = &list[b.launch_index];
+            for (int q = c->first; q < c->second; ++q) list[r0 + q].chain = (int)ex->chains.size();
+            list[r0 + c->first].chain_head = true;
+            ex->chains.push_back(std::move(ch));
+        }
+        r0 = r1;
     }
 }
 
