@@ -197,6 +197,11 @@ struct Chain {
     std::vector<Block> hblocks;
 };
 
+// Modelled times of one tile job on each tile shape: all its tiles, one tile.
+struct TileCosts {
+    std::array<double, K_MFMA_TILES> all, one;
+};
+
 struct PlanExec {
     const Plan* plan;
     const Terms* terms;
@@ -249,6 +254,7 @@ struct tn_exec_s {
     std::vector<tn::Chain> chains;
     bool probe = false;                     // built for its shapes only (see build_exec)
     bool narrow = false;                    // split sums with less scratch (see build_fitting)
+    std::map<int, std::vector<tn::TileCosts>> tile_costs;   // a probe's FP32 tile jobs, by level
     int64_t bare_bytes = 0;                 // without tile lists and scratch: no tile choice needs less
     // packed circuits: the tail runs as one finalize and one level-sum launch
     // the tail of all packed circuits: one record per circuit, the per-block
@@ -355,6 +361,9 @@ constexpr double kSmallJobShare = 0.25;
 // One launch in tile-model units (the 25-qubit workload's 512-tile 128 x 64
 // launch of k = 8 models at 1.0e8 and runs 15 us; a launch costs about 5 us).
 constexpr double kLaunchCost = 3.5e7;
+// A level of packed circuits above this many units (about 0.5 ms of full tiles) is
+// heavy: its tile shapes are chosen by their work rather than for one launch.
+constexpr double kHeavyLevel = 5e9;
 // A FP32 tree level with less work than this (summed over its steps) runs all
 // its steps in its small-step launch: a grouped tile launch of its own costs
 // more than the tiles save (a dependent launch costs about 10 us end to end).
@@ -562,6 +571,8 @@ struct Builder {
     // FP32 tile shape imposed per tree level on jobs of at most the given
     // flops (the small jobs join the level's main matrix-core launch)
     const std::map<int, std::pair<int, double>>* level_tile = nullptr;
+    // packed circuits: the tile shapes an FP32 tree level may use (bits; none: all)
+    const std::map<int, unsigned>* level_shapes = nullptr;
     // FP32 tree levels with little work: every step runs in the level's
     // small-step launch (one launch instead of one per tile shape plus one)
     const std::set<int>* small_levels = nullptr;
@@ -666,22 +677,29 @@ struct Builder {
         // the weights stand for beside the rate is how short a level's last round over the
         // CUs is, how many tiles its setup and reduction have and, for packed circuits,
         // that each further shape in a level is one more launch.)  kEffNarrow is from
-        // before 128 x 32 had 32-row waves.  Packed circuits: twelve 2020 us with it, 1689
-        // with kEffPacked; of 15 drawn sets 12 are 7 to 35 % faster, three of 7 to 17 ms 1
-        // to 2 % slower.  One circuit alone: with kEffPacked a 36-qubit QAOA's 8208 slices
+        // before 128 x 32 had 32-row waves.  Packed circuits: twelve 2020 us with it, 1690
+        // with kEffPacked; their heavy levels have weights nearer the rates (kEffHeavy,
+        // packed_shapes).  One circuit alone: with kEffPacked a 36-qubit QAOA's 8208 slices
         // of 8 x 16 outputs over 1024 terms run half padded on 128 x 32 (376 us; 261 on 32
         // x 16), the estimate takes 920 us, 815 with kEffNarrow, 812 with kEffOne (25-qubit
         // grid 1092 -> 1064, a range of amplitudes 985 -> 882), which has the 16-wide tiles
         // higher.  kEffOne was chosen on 48 drawn circuits; on 26 others it is 2.9 % faster
         // than kEffNarrow and 0.6 % than kEffPacked in the mean, at most 2 % slower than
-        // either.  The rates of full launches as weights: the amplitudes 1213 us, the
-        // packed circuits 1974.
+        // either.  The rates of full launches as weights everywhere: the amplitudes 1213
+        // us, four 16-qubit targets 181 -> 205.
         static const double kEffPacked[K_MFMA_TILES] = {0.95, 0.6, 1.0, 0.5, 0.35, 0.45, 0.3, 0.2};
+        static const double kEffHeavy[K_MFMA_TILES] = {1.0, 0.8, 0.85, 0.6, 0.4, 0.5, 0.35, 0.27};
         static const double kEffOne[K_MFMA_TILES] = {0.95, 0.6, 1.0, 0.5, 0.35, 0.5, 0.35, 0.27};
         // for a small workspace (build_fitting): 128 x 32 is taken less often, whose
         // split sums need more scratch than the smaller tiles'
         static const double kEffNarrow[K_MFMA_TILES] = {1.0, 0.6, 0.75, 0.5, 0.35, 0.45, 0.3, 0.2};
-        const double* kEff = narrow ? kEffNarrow : quantize_tiles ? kEffOne : kEffPacked;
+        const bool per_estimate = !fp64 && !(fold_const && C.mask == 0);
+        unsigned shapes = ~0u;
+        if (per_estimate && level_shapes && level_shapes->count(st.level)) shapes = level_shapes->at(st.level);
+        const double* kEff = narrow           ? kEffNarrow
+                             : quantize_tiles ? kEffOne
+                             : shapes != ~0u  ? kEffHeavy
+                                              : kEffPacked;
         static const double kEff64[K_MFMA_TILES] = {0, 1.0, 0, 0, 0.7, 0, 0, 0};
         const int rk = (int)K.size();
         const int64_t ns = ninst * nbatch;
@@ -704,6 +722,8 @@ struct Builder {
             const double job_flops = 8.0 * std::ldexp((double)ns, (int)(FA.size() + FB.size()) + rk);
             if (job_flops <= lt.second) forced = lt.first;
         }
+        TileCosts costs;
+        costs.all.fill(1e300);
         double best_cost = 1e300, forced_cost = 1e300;
         int best_o = 0, best_tile = 0, best_merge = 0, forced_o = 0, forced_merge = 0;
         for (int o = 0; o < 2; ++o) {
@@ -733,7 +753,9 @@ struct Builder {
                     const int64_t eff_tiles =
                         !quantize_tiles ? tiles : std::max<int64_t>(1, (tiles + kNumCUs - 1) / kNumCUs) * kNumCUs;
                     const double cst = (double)eff_tiles * per_tile;
-                    if (cst < best_cost) {
+                    costs.one[tile] = per_tile * kEff[tile] / kEffHeavy[tile];
+                    costs.all[tile] = std::min(costs.all[tile], (double)eff_tiles * costs.one[tile]);
+                    if (cst < best_cost && (shapes >> tile & 1u)) {
                         best_cost = cst;
                         best_o = o;
                         best_tile = tile;
@@ -760,6 +782,7 @@ struct Builder {
                 }
             }
         }
+        if (per_estimate && ex->probe) ex->tile_costs[st.level].push_back(costs);
         // a shape imposed by the level takes over when it costs this job at most
         // about one launch more than its own best shape (the launch it saves)
         // (a tuned level's shape, max flops = infinity, is imposed on every job)
@@ -1818,10 +1841,12 @@ static void place_outputs(tn_exec_s* ex) {
 
 static void build_schedule(tn_exec_s* ex, int n, const tn_plan* plans, const tn_terms* terms,
                            const std::map<int, std::pair<int, double>>* level_tile = nullptr,
-                           TermRange range = TermRange{}, const std::set<int>* small_levels = nullptr) {
+                           TermRange range = TermRange{}, const std::set<int>* small_levels = nullptr,
+                           const std::map<int, unsigned>* level_shapes = nullptr) {
     Builder bw;
     bw.ex = ex;
     bw.level_tile = level_tile;
+    bw.level_shapes = level_shapes;
     bw.small_levels = small_levels;
     bw.grouping = ex->opts.no_group == 0;
     bw.quantize_tiles = n == 1;
@@ -2720,6 +2745,41 @@ static void fill_results(tn_exec_s* ex, const void* base, tn_result* results) {
     }
 }
 
+// Tile shapes (bits) of a heavy level of packed circuits: those with the least
+// modelled time.  Each shape is a launch of its own, which takes whole rounds over the
+// compute units, at least one of its longest tile, and twice a launch's cost (its
+// start and its end, where the chip empties).  0: the level is not heavy.
+// kEffPacked alone puts 9 x 6 bits over 2^10 terms on 128 x 32 tiles, 12 ms instead of
+// the 2.8 of 128 x 64 (their rows are read twice as often).
+static unsigned packed_shapes(const std::vector<TileCosts>& jobs) {
+    double least = 0;
+    for (const TileCosts& j : jobs) least += *std::min_element(j.all.begin(), j.all.end());
+    if (least < kHeavyLevel) return 0;
+    unsigned best = 0;
+    double best_t = 1e300;
+    for (unsigned set = 1; set < 1u << K_MFMA_TILES; ++set) {
+        std::array<double, K_MFMA_TILES> all{}, one{}, tiles{};
+        for (const TileCosts& j : jobs) {
+            int at = -1;
+            for (int t = 0; t < K_MFMA_TILES; ++t)
+                if ((set >> t & 1u) && (at < 0 || j.all[t] < j.all[at])) at = t;
+            all[at] += j.all[at];
+            one[at] = std::max(one[at], j.one[at]);
+            tiles[at] += j.all[at] / j.one[at];
+        }
+        double time = 0;
+        for (int t = 0; t < K_MFMA_TILES; ++t)
+            if (tiles[t] > 0)
+                time += 2 * kLaunchCost + std::max(std::ceil(tiles[t] / kNumCUs) * kNumCUs * (all[t] / tiles[t]),
+                                               kNumCUs * one[t]);
+        if (time < best_t) {
+            best_t = time;
+            best = set;
+        }
+    }
+    return best;
+}
+
 // Host part of tn_exec_prepare: the schedule of n packed plans over the terms
 // in `range`, with its constant region staged on the host (no device call).
 static std::unique_ptr<tn_exec_s> build_exec(int n, const tn_plan* plans, const tn_terms* terms,
@@ -2786,8 +2846,12 @@ static std::unique_ptr<tn_exec_s> build_exec(int n, const tn_plan* plans, const 
             }
         ex->small_levels = small;
         ex->level_tile = level_tile;
+        std::map<int, unsigned> level_shapes;
+        if (n > 1 && !ex->narrow && !ex->opts.mixed_shapes)
+            for (auto& kv : probe.tile_costs)
+                if (const unsigned shapes = packed_shapes(kv.second)) level_shapes[kv.first] = shapes;
         build_schedule(ex.get(), n, plans, terms, level_tile.empty() ? nullptr : &level_tile, range,
-                       small.empty() ? nullptr : &small);
+                       small.empty() ? nullptr : &small, level_shapes.empty() ? nullptr : &level_shapes);
     } else {
         build_schedule(ex.get(), n, plans, terms, nullptr, range);
     }
